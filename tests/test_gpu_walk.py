@@ -1,0 +1,86 @@
+"""The column walk's reconstruction and flux where their case distinctions
+sit: rough states (the constraint's every case, extrema on every line),
+plateaus and exact ties, and a NaN next to a cell, which must reach the flux.
+
+Tolerance: the parity bounds of tests/parity.py (1e-12 per field and per
+element): each value is formed from at most a few hundred operations on
+operands of the local scale."""
+import numpy as np
+import pytest
+
+from parity import check
+from paper_2107_10987_amd.workloads import PERIODIC, uniform_tree
+
+pytestmark = pytest.mark.gpu
+
+GAMMA = 5.0 / 3.0
+
+
+def state(kind, n, seed):
+    r = np.random.default_rng(seed)
+    shape = (n, 8, 8, 8)
+    if kind == "rough":          # every cell its own value
+        draw = lambda lo, hi: r.uniform(lo, hi, shape)  # noqa: E731
+    elif kind == "ties":         # few distinct values: equal neighbours, equal differences
+        draw = lambda lo, hi: lo + (hi - lo) * r.integers(0, 3, shape) / 2.0  # noqa: E731
+    else:                        # steps between plateaus
+        draw = lambda lo, hi: np.where(r.integers(0, 2, (n, 2, 2, 2)).repeat(4, 1).repeat(4, 2).repeat(4, 3) > 0, lo, hi)  # noqa: E731
+    rho = draw(1.0, 3.0)
+    v = [draw(-0.5, 0.5) for _ in range(3)]
+    e = draw(1.0, 2.0)
+    U = np.stack([rho, rho * v[0], rho * v[1], rho * v[2], e + 0.5 * rho * sum(x * x for x in v), e ** (1 / GAMMA),
+                  rho * draw(0.0, 1.0)], axis=1)
+    return np.ascontiguousarray(U)
+
+
+@pytest.mark.parametrize("kind", ["rough", "ties", "plateaus"])
+def test_walk_against_oracle(kind):
+    import torch
+    import oracle
+    from paper_2107_10987_amd.hydro import Hydro
+    t = uniform_tree((3, 2, 2), (PERIODIC,) * 3, (-0.2, 0.1, 0.0), 1.0 / 16)
+    U = state(kind, t.n, 11)
+    print("case:", kind, flush=True)
+    o = oracle.Oracle(t, GAMMA, 0.3)
+    hy = Hydro(max_leaves=t.n, schedule="column")
+    try:
+        g = hy.grid(t, torch.tensor(U, device="cuda"), 0.3, GAMMA)
+        dt = 0.2 * o.dt(U)
+        want, a = o.stage(1, dt, U)
+        out = torch.empty_like(g.U)
+        am = torch.zeros(t.n, dtype=torch.float64, device="cuda")
+        hy.stage(g, 1, dt, g.U, None, out, am)
+        assert np.abs(am.cpu().numpy() - a).max() <= 1e-12 * a.max()
+        check(out.cpu().numpy(), want, o, U, label=kind)
+    finally:
+        hy.close()
+
+
+@pytest.mark.parametrize("cell", [(-1, 3, 3), (8, 0, 7), (2, -1, 5), (4, 4, 8), (-1, -1, 3), (8, 2, -1), (8, 8, 8),
+                                  (-1, 8, -1)])
+def test_nan_beside_a_cell_is_reported(cell):
+    """A ghost cell without a value (a prolongation row that does not exist)
+    is NaN; it touches an interior cell by a face, an edge or a corner."""
+    import torch
+    from paper_2107_10987_amd import hydro
+    t = uniform_tree((1, 1, 1), (PERIODIC,) * 3, (0.0, 0.0, 0.0), 1.0 / 8)
+    U = state("rough", 1, 3)
+    print("case: NaN at", cell, flush=True)
+    gm = hydro.ghost_map(t).copy()
+    slot = 0
+    for k in range(-3, 11):
+        for j in range(-3, 11):
+            for i in range(-3, 11):
+                if 0 <= i < 8 and 0 <= j < 8 and 0 <= k < 8:
+                    continue
+                if (i, j, k) == cell:
+                    gm[0, slot] = -(1 << 30) - 1
+                slot += 1
+    hy = hydro.Hydro(max_leaves=1, schedule="column")
+    try:
+        g = hy.grid(t, torch.tensor(U, device="cuda"), 0.0, GAMMA, gmap=gm)
+        with pytest.raises(hydro.HydroError) as e:
+            hy.step(g, 1e-4)
+        assert e.value.code == hydro.ENONPHYS
+    finally:
+        hy.close()
