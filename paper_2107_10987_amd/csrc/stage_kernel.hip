@@ -31,6 +31,14 @@ namespace {
 constexpr int NT = FACES_PER_AXIS;  // 576 threads: one face per axis each
 constexpr int SX_ = 1, SY_ = PB, SZ_ = PB * PB;
 
+// Distance of two fields' 14^3 planes in the LDS block: one row less than a
+// plane, so that four planes lie within a load's 16-bit offset of one address
+// (3 * 2730 * 8 = 65,520 B; whole planes would reach three).  The last row of a
+// plane (j = k = 10) and the first of the next (j = k = -3) share their place:
+// no stencil reads a cell that is outermost along two axes.
+constexpr int PS = NP - PB;
+constexpr int BLOCK_LDS = (NF - 1) * PS + NP;
+
 __constant__ uint16_t c_ghost_pad[NG];  // padded index of each ghost slot
 
 __device__ __forceinline__ int pidx(int i, int j, int k) {
@@ -138,7 +146,7 @@ __device__ __forceinline__ void point_state(const double *P, int c, int dx, int 
     st = plus ? st : -st;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-        U[f] = ppm_end(P + f * NP, c, st, plus);
+        U[f] = ppm_end(P + f * PS, c, st, plus);
         __builtin_amdgcn_sched_barrier(0);   // bound the loads in flight (register pressure)
     }
 }
@@ -151,11 +159,10 @@ __device__ __forceinline__ void point_state(const double *P, int c, int dx, int 
 // instead of an infinity, and the stage reports the non-physical result
 // either way.
 __device__ __forceinline__ double rcp_nr(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
+    // r (1 + e + e^2): e of the estimate is below 2^-24, e^3 below an ulp
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, __builtin_fma(e, e, e), r);
 }
 __device__ __forceinline__ double sqrt_nr(double x) {
     const double y = __builtin_amdgcn_rsq(x);
@@ -165,7 +172,8 @@ __device__ __forceinline__ double sqrt_nr(double x) {
     h = __builtin_fma(h, r, h);
     const double d = __builtin_fma(-g, g, x);
     g = __builtin_fma(d, h, g);
-    return x == 0.0 ? x : g;
+    // at zero g is 0 * inf, the default NaN, whose low word is zero
+    return __hiloint2double(x == 0.0 ? 0 : __double2hiint(g), __double2loint(g));
 }
 
 // What the flux along an axis needs of one reconstructed state: normal
@@ -325,17 +333,17 @@ __device__ __forceinline__ void gather_block(double *P, const double *U, const i
     for (int i = 0; i < NI; ++i) {
         const int e = min(tid + i * NTH, LEAF_STRIDE - 1);
         const int f = e >> 9, c = e & (NC - 1);
-        P[f * NP + pidx(c & 7, (c >> 3) & 7, c >> 6)] = v[i];
+        P[f * PS + pidx(c & 7, (c >> 3) & 7, c >> 6)] = v[i];
     }
 #pragma unroll
     for (int i = 0; i < NGI; ++i) {
         const int src = srcs[i];
         if (src >= 0) {
 #pragma unroll
-            for (int f = 0; f < NF; ++f) P[f * NP + pads[i]] = gv[i][f];
+            for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = gv[i][f];
         } else if (src < -PROLONG_BASE) {
 #pragma unroll 1
-            for (int f = 0; f < NF; ++f) P[f * NP + pads[i]] = ghost_value(U, src, f, lg, prolong, n_prolong);
+            for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = ghost_value(U, src, f, lg, prolong, n_prolong);
         } else {
             const double *q = U + src_offset(-src - 1, lg);
 #pragma unroll
@@ -350,7 +358,7 @@ __device__ __forceinline__ void gather_block(double *P, const double *U, const i
                 acc = acc + qf[E2 + 1];
                 acc = acc + qf[E2 + E];
                 acc = acc + qf[E2 + E + 1];
-                P[f * NP + pads[i]] = acc * 0.125;
+                P[f * PS + pads[i]] = acc * 0.125;
             }
         }
     }
@@ -467,7 +475,7 @@ __device__ __forceinline__ void store_amax(const StageArgs &a, int leaf, const d
 }
 
 __global__ void __launch_bounds__(NT) stage_kernel(StageArgs a) {
-    __shared__ double P[NF * NP];
+    __shared__ double P[BLOCK_LDS];
     const int leaf = a.leaf0 + xcd_leaf(blockIdx.x, gridDim.x);
     const int tid = threadIdx.x;
 
@@ -545,37 +553,36 @@ constexpr int NTC = 768;            // 12 waves x 64 lanes: three per SIMD
 constexpr int COLS_PER_WAVE = 6;    // 6 columns x 10 cells = 60 lanes
 
 // PPM on five values along a line, as the column walk computes it: the limited
-// parabola of ppm_vals in differences from the middle value, in 50
+// parabola of ppm_vals in differences from the middle value, in 46
 // instructions without a branch where ppm_vals takes 67 with its constraint's
 // branches (the walk issues VALU instructions nearly all the time, so each is
 // time: with the flux below, two steps of a 34,000-leaf binary went from 56.6
-// to 49.3 ms, of 512 blocks of a transonic flow by RK3 from 1.21 to 1.02 ms).
+// to 47.0 ms, of 512 blocks of a transonic flow by RK3 from 1.21 to 0.97 ms).
 // With d1..d4 the four differences and sm, s0, sp the limited slopes,
 //   X = 6 (R - q2) = 3 d3 + s0 - sp,   Y = 6 (q2 - L) = 3 d2 + s0 - sm,
 // and the CW84 constraint reads: both zero where X and Y have opposite signs
-// (an extremum; a zero clamps the other to zero below), else each at most
-// twice the other (D M6 > D^2 is Y > 2 X, D M6 < -D^2 is X > 2 Y).  The
-// comparisons keep a NaN, and t = 0 keeps one too, so a NaN next to the cell
-// reaches the flux as it does through ppm_vals.  Results agree with ppm_vals
-// to the rounding of the offsets.
+// (an extremum), else each at most twice the other (D M6 > D^2 is Y > 2 X,
+// D M6 < -D^2 is X > 2 Y): X clamped to the interval between 0 and 2 Y, Y to
+// that between 0 and 2 X.  min and max pass over a NaN; 0 (d2 + d3) / 4 keeps
+// one, so a NaN next to the cell reaches the flux as it does through ppm_vals.
+// Results agree with ppm_vals to the rounding of the offsets.
 __device__ __forceinline__ void ppm_walk(double q0, double q1, double q2, double q3, double q4, double &left,
                                          double &right) {
     const double d1 = q1 - q0, d2 = q2 - q1, d3 = q3 - q2, d4 = q4 - q3;
     const double h2 = 0.25 * d2, h3 = 0.25 * d3;
-    const double mm = fmin(fmin(fabs(d1), fabs(d2)), fabs(__builtin_fma(0.25, d1, h2)));
     const double m0 = fmin(fmin(fabs(d2), fabs(d3)), fabs(h2 + h3));
+    const double mm = fmin(fmin(fabs(d1), fabs(d2)), fabs(__builtin_fma(0.25, d1, h2)));
     const double mp = fmin(fmin(fabs(d3), fabs(d4)), fabs(__builtin_fma(0.25, d4, h3)));
     const double sm = copysign(mm, d1) + copysign(mm, d2);
     const double s0 = copysign(m0, d2) + copysign(m0, d3);
     const double sp = copysign(mp, d3) + copysign(mp, d4);
     const double X = __builtin_fma(3.0, d3, s0 - sp), Y = __builtin_fma(3.0, d2, s0 - sm);
     const double X2 = X + X, Y2 = Y + Y;
-    int sxy = __double2hiint(X) ^ __double2hiint(Y);
-    asm("" : "+v"(sxy));   // or the sign test becomes a 64-bit one
-    const double t = sxy < 0 ? 0.0 : 1.0 / 6.0;
-    const double Xc = fabs(X) > fabs(Y2) ? Y2 : X, Yc = fabs(Y) > fabs(X2) ? X2 : Y;
-    right = __builtin_fma(Xc, t, q2);
-    left = __builtin_fma(-Yc, t, q2);
+    const double Xc = fmax(fmin(Y2, 0.0), fmin(X, fmax(Y2, 0.0)));
+    const double Yc = fmax(fmin(X2, 0.0), fmin(Y, fmax(X2, 0.0)));
+    const double q = __builtin_fma(0.0, h2 + h3, q2);
+    right = __builtin_fma(Xc, 1.0 / 6.0, q);
+    left = __builtin_fma(-Yc, 1.0 / 6.0, q);
     // formed here: sunk to their uses behind the flux's branches, the selects
     // would keep four registers alive per value instead of two
     asm volatile("" : "+v"(right), "+v"(left));
@@ -589,20 +596,29 @@ __device__ __forceinline__ void ppm_walk(double q0, double q1, double q2, double
 // computed once and used by both of its cells).
 __device__ __forceinline__ void line_ends(const double *P, int c, int dx, int dy, int dz,
                                           double pos[NF], double neg[NF]) {
+    // one LDS address per stencil point, made opaque so that the fields are
+    // reached by the loads' immediate offsets (four fields each) instead of
+    // the strides being added up again for every field
     const int st = dx * SX_ + dy * SY_ + dz * SZ_;
-    const double *q = P + c;
-    double a0 = q[-2 * st], a1 = q[-st], a2 = q[0], a3 = q[st], a4 = q[2 * st];
+    typedef const __attribute__((address_space(3))) double *lds;
+    lds p0 = (lds)(P + c) - 2 * st, p1 = p0 + st, p2 = p1 + st, p3 = p2 + st, p4 = p3 + st;
+    asm("" : "+v"(p0), "+v"(p1), "+v"(p2), "+v"(p3), "+v"(p4));
+    double a0 = *p0, a1 = *p1, a2 = *p2, a3 = *p3, a4 = *p4;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         // the next field's stencil is loaded while this one is reconstructed
         double b0 = 0.0, b1 = 0.0, b2 = 0.0, b3 = 0.0, b4 = 0.0;
         if (f + 1 < NF) {
-            const double *qn = q + (f + 1) * NP;
-            b0 = qn[-2 * st];
-            b1 = qn[-st];
-            b2 = qn[0];
-            b3 = qn[st];
-            b4 = qn[2 * st];
+            if (f + 1 == 4) {
+                p0 += 4 * PS, p1 += 4 * PS, p2 += 4 * PS, p3 += 4 * PS, p4 += 4 * PS;
+                asm("" : "+v"(p0), "+v"(p1), "+v"(p2), "+v"(p3), "+v"(p4));
+            }
+            const int o = (f + 1) % 4 * PS;
+            b0 = p0[o];
+            b1 = p1[o];
+            b2 = p2[o];
+            b3 = p3[o];
+            b4 = p4[o];
         }
         ppm_walk(a0, a1, a2, a3, a4, neg[f], pos[f]);
         // keep the scheduler from hoisting further fields' stencil loads:
@@ -645,7 +661,7 @@ __device__ __forceinline__ void line_vals(const double *P, int c, int dx, int dy
         for (int f = 0; f < NF; ++f) o[f] = line_offsets(src.off, f, dx, dy, dz);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            const double qc = P[f * NP + c];
+            const double qc = P[f * PS + c];
             pos[f] = qc + (double)o[f].x;
             neg[f] = qc + (double)o[f].y;
         }
@@ -670,7 +686,7 @@ __device__ __forceinline__ void pair_vals(const double *P, int c, int x1, int y1
         }
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            const double qc = P[f * NP + c];
+            const double qc = P[f * PS + c];
             pos1[f] = qc + (double)o1[f].x;
             neg1[f] = qc + (double)o1[f].y;
             pos2[f] = qc + (double)o2[f].x;
@@ -863,7 +879,7 @@ __device__ __forceinline__ void col_finish_leaf(const StageArgs &a, int leaf, co
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             dsum[f] = (W[(0 * NF + f) * NC + c] + W[(1 * NF + f) * NC + c]) + W[(2 * NF + f) * NC + c];
-            u[f] = P[f * NP + pc];
+            u[f] = P[f * PS + pc];
         }
         finish_cell_u(a, leaf, c, dx, dt, dsum, u);
     }
@@ -904,7 +920,7 @@ __device__ __forceinline__ void block_max(double smax, double *red, int tid) {
 // the three slices.
 template <bool LEARNED>
 __global__ void __launch_bounds__(NTC) stage_kernel_col(StageArgs a) {
-    __shared__ double P[NF * NP];
+    __shared__ double P[BLOCK_LDS];
     __shared__ int next_task;
     const int leaf = a.leaf0 + xcd_leaf(blockIdx.x, gridDim.x);
     const int tid = threadIdx.x;
@@ -946,7 +962,7 @@ __device__ __forceinline__ int next_item(int *queue, int items, int xcd) {
 }
 template <bool LEARNED>
 __global__ void __launch_bounds__(NTC) stage_kernel_col_persistent(StageArgs a) {
-    __shared__ double P[NF * NP];
+    __shared__ double P[BLOCK_LDS];
     __shared__ int item_s, last_s, next_task;
     const int tid0 = threadIdx.x;
     const int T = a.tiles;
@@ -1092,7 +1108,7 @@ __global__ void __launch_bounds__(NTR) reflux_kernel(RefluxArgs r) {
 __global__ void __launch_bounds__(NT) reconstruct_kernel(const double *U, const int32_t *gm,
                                                          const int32_t *prolong, int n_prolong,
                                                          double *out) {
-    __shared__ double P[NF * NP];
+    __shared__ double P[BLOCK_LDS];
     const int leaf = blockIdx.x;
     gather_block<NT>(P, U, gm, leaf, 0, 3, prolong, n_prolong, threadIdx.x);
     __syncthreads();
@@ -1147,7 +1163,7 @@ hipError_t hydro_launch_stage(const StageArgs &a, hipStream_t s) {
 __global__ void __launch_bounds__(NT) pairs_kernel(const double *U, const int32_t *gm,
                                                    const int32_t *prolong, int n_prolong, float *X,
                                                    float *T, uint8_t *valid) {
-    __shared__ double P[NF * NP];
+    __shared__ double P[BLOCK_LDS];
     const int leaf = blockIdx.x;
     gather_block<NT>(P, U, gm, leaf, 0, 3, prolong, n_prolong, threadIdx.x);
     __syncthreads();
@@ -1155,7 +1171,7 @@ __global__ void __launch_bounds__(NT) pairs_kernel(const double *U, const int32_
         const int c = e / NF, f = e - (e / NF) * NF;
         const int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
         const int pc = pidx(i, j, k);
-        const double *q = P + f * NP;
+        const double *q = P + f * PS;
         const double qc = q[pc];
         double sigma = 0.0;
         for (int o = 0; o < 27; ++o) {
