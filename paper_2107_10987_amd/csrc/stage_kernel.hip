@@ -563,10 +563,10 @@ constexpr int COLS_PER_WAVE = 6;    // 6 columns x 10 cells = 60 lanes
 // and the CW84 constraint reads: both zero where X and Y have opposite signs
 // (an extremum), else each at most twice the other (D M6 > D^2 is Y > 2 X,
 // D M6 < -D^2 is X > 2 Y): X clamped to the interval between 0 and 2 Y, Y to
-// that between 0 and 2 X.  min and max pass over a NaN; 0 (d2 + d3) / 4 keeps
-// one, so a NaN next to the cell reaches the flux as it does through ppm_vals.
-// Results agree with ppm_vals to the rounding of the offsets.
-__device__ __forceinline__ void ppm_walk(double q0, double q1, double q2, double q3, double q4, double &left,
+// that between 0 and 2 X.  Results agree with ppm_vals to the rounding of the
+// offsets; where X or Y is a NaN, which the clamps pass over, the line is to be
+// taken from ppm_vals (returns whether).
+__device__ __forceinline__ bool ppm_walk(double q0, double q1, double q2, double q3, double q4, double &left,
                                          double &right) {
     const double d1 = q1 - q0, d2 = q2 - q1, d3 = q3 - q2, d4 = q4 - q3;
     const double h2 = 0.25 * d2, h3 = 0.25 * d3;
@@ -580,12 +580,12 @@ __device__ __forceinline__ void ppm_walk(double q0, double q1, double q2, double
     const double X2 = X + X, Y2 = Y + Y;
     const double Xc = fmax(fmin(Y2, 0.0), fmin(X, fmax(Y2, 0.0)));
     const double Yc = fmax(fmin(X2, 0.0), fmin(Y, fmax(X2, 0.0)));
-    const double q = __builtin_fma(0.0, h2 + h3, q2);
-    right = __builtin_fma(Xc, 1.0 / 6.0, q);
-    left = __builtin_fma(-Yc, 1.0 / 6.0, q);
+    right = __builtin_fma(Xc, 1.0 / 6.0, q2);
+    left = __builtin_fma(-Yc, 1.0 / 6.0, q2);
     // formed here: sunk to their uses behind the flux's branches, the selects
     // would keep four registers alive per value instead of two
     asm volatile("" : "+v"(right), "+v"(left));
+    return __builtin_isunordered(X, Y);
 }
 
 // Both ends of the line through padded cell c along d = (dx,dy,dz) for all
@@ -596,6 +596,7 @@ __device__ __forceinline__ void ppm_walk(double q0, double q1, double q2, double
 // computed once and used by both of its cells).
 __device__ __forceinline__ void line_ends(const double *P, int c, int dx, int dy, int dz,
                                           double pos[NF], double neg[NF]) {
+    bool bad = false;
     // one LDS address per stencil point, made opaque so that the fields are
     // reached by the loads' immediate offsets (four fields each) instead of
     // the strides being added up again for every field
@@ -620,7 +621,7 @@ __device__ __forceinline__ void line_ends(const double *P, int c, int dx, int dy
             b3 = p3[o];
             b4 = p4[o];
         }
-        ppm_walk(a0, a1, a2, a3, a4, neg[f], pos[f]);
+        bad |= ppm_walk(a0, a1, a2, a3, a4, neg[f], pos[f]);
         // keep the scheduler from hoisting further fields' stencil loads:
         // all seven at once cost ~70 VGPRs and force spills at 12 waves per CU
         __builtin_amdgcn_sched_barrier(0);
@@ -629,6 +630,14 @@ __device__ __forceinline__ void line_ends(const double *P, int c, int dx, int dy
         a2 = b2;
         a3 = b3;
         a4 = b4;
+    }
+    if (__builtin_expect(bad, 0)) {
+        const double *qc = P + c;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            ppm_both(qc + f * PS, 0, st, neg[f], pos[f]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
 }
 
