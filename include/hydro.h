@@ -58,7 +58,8 @@ typedef struct hydro_t hydro_t;
 #define HYDRO_SCHED_FACE 1        /* a workgroup per leaf, one face of each axis per thread       */
 #define HYDRO_SCHED_COLUMN 2      /* a workgroup per leaf, lanes walk cell columns (1.71x PPM)    */
 #define HYDRO_SCHED_PERSISTENT 3  /* one workgroup per compute unit pulling leaves from a queue  */
-#define HYDRO_SCHED_TILED 4       /* persistent, queue of (leaf, axis) items: 3x the parallelism */
+#define HYDRO_SCHED_TILED 4       /* 2 to 8 workgroups per leaf where all run at once, else a queue
+                                     of (leaf, axis) items: up to 8x the parallelism */
 #define HYDRO_NBUCKET 16          /* autotune buckets: launch size in [2^b, 2^(b+1))             */
 
 /* Library-wide settings fixed at creation. */

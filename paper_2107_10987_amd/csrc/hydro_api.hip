@@ -36,7 +36,7 @@ struct hydro_t {
     hipEvent_t fork_ev = nullptr;
     hipEvent_t join_ev[NSIDE] = {};
     int *leaf_done = nullptr;  // [max_leaves]
-    double *tile_amax = nullptr;  // [max_leaves][3]
+    double *tile_amax = nullptr;  // [max_leaves][MAX_PARTS]
     double *bflux = nullptr;   // flux correction: [max_leaves][6][7][64]
     int num_cu = 0;
     int32_t table[HYDRO_NBUCKET];  // schedule per launch-size bucket (HYDRO_SCHED_AUTO)
@@ -211,22 +211,37 @@ int bucket_of(int nleaf) {
 // with the per-size table's schedule.
 constexpr int MULTI_MERGE = 5;
 
-// Schedule of a launch of nleaf leaves.
-int resolve_schedule(const hydro_t *h, int nleaf, bool concurrent) {
+// Schedule of a launch of nleaf of the stage's nstage blocks.
+int resolve_schedule(const hydro_t *h, int nleaf, int nstage, bool concurrent) {
     if (h->p.schedule != HYDRO_SCHED_AUTO) return h->p.schedule;
     if (concurrent && h->multi_sched >= 0 && h->multi_sched != MULTI_MERGE) return h->multi_sched;
     if (h->table_loaded) return h->table[bucket_of(nleaf)];
-    // built-in rule: spread small launches over (leaf, axis) tiles so they
-    // still occupy most compute units; otherwise a workgroup per leaf
-    return (3 * nleaf <= h->num_cu) ? HYDRO_SCHED_TILED : HYDRO_SCHED_COLUMN;
+    // built-in rule: parts of leaves where whole ones leave half the chip idle
+    return (2 * nstage <= h->num_cu) ? HYDRO_SCHED_TILED : HYDRO_SCHED_COLUMN;
 }
 
-void set_schedule(StageArgs &a, int sched) {
+// alone: no other launch of the stage runs beside this one.
+void set_schedule(const hydro_t *h, StageArgs &a, int sched, bool alone) {
+    a.kernel = KERNEL_COLUMN;
+    a.tiles = 1;
+    a.whole = a.nleaf;
     switch (sched) {
-    case HYDRO_SCHED_FACE: a.kernel = KERNEL_FACE; a.tiles = 1; break;
-    case HYDRO_SCHED_PERSISTENT: a.kernel = KERNEL_PERSISTENT; a.tiles = 1; break;
-    case HYDRO_SCHED_TILED: a.kernel = KERNEL_PERSISTENT; a.tiles = 3; break;
-    default: a.kernel = KERNEL_COLUMN; a.tiles = 1; break;
+    case HYDRO_SCHED_FACE: a.kernel = KERNEL_FACE; break;
+    case HYDRO_SCHED_PERSISTENT: a.kernel = KERNEL_PERSISTENT; break;
+    case HYDRO_SCHED_TILED:
+        a.tiles = leaf_parts(a.nleaf, h->num_cu);
+        a.whole = 0;
+        if (a.tiles == 1) {   // a queue of axis tiles
+            a.kernel = KERNEL_PERSISTENT;
+            a.tiles = 3;
+        }
+        break;
+    default:
+        // a last round that would leave half the chip idle runs as parts
+        if (alone && a.nleaf > h->num_cu && a.nleaf % h->num_cu) {
+            a.tiles = leaf_parts(a.nleaf % h->num_cu, h->num_cu);
+            if (a.tiles > 1) a.whole = a.nleaf - a.nleaf % h->num_cu;
+        }
     }
 }
 
@@ -302,7 +317,7 @@ int run_stage(hydro_t *h, const hydro_grid *g, int stage, double dt, const doubl
         const int j = k++ % nst;
         const hipStream_t st = j == 0 ? s : h->side[j - 1];
         a.queue = h->queue + QUEUE_INTS * j;
-        set_schedule(a, resolve_schedule(h, a.nleaf, nst > 1));
+        set_schedule(h, a, resolve_schedule(h, a.nleaf, g->n << h->ts, nst > 1), nst == 1);
         if (h->p.recon == 1) {
             // the network's point values and per-cell verdicts for this launch
             mlp::MlpInfer m{};
@@ -677,7 +692,7 @@ int hydro_create(const hydro_params *p, hydro_t **out) {
     }
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipMalloc((void **)&h->leaf_done, n * sizeof(int));
-    if (e == hipSuccess) e = hipMalloc((void **)&h->tile_amax, n * 3 * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc((void **)&h->tile_amax, n * MAX_PARTS * sizeof(double));
     if (e == hipSuccess && p->reflux) e = hipMalloc((void **)&h->bflux, n * BFLUX_STRIDE * sizeof(double));
     if (e == hipSuccess) e = alloc_mlp(h, n);
     if (e == hipSuccess) e = hipMemset(h->queue, 0, QUEUE_INTS * (1 + NSIDE) * sizeof(int));

@@ -34,6 +34,8 @@ struct Status {
     int field;
 };
 
+constexpr int MAX_PARTS = 8;   // workgroups a leaf is split over
+
 struct StageArgs {
     const double *Uin;        // [n][7][512] stage input (ghost source)
     const double *Un;         // [n][7][512] step start (stage 2)
@@ -55,13 +57,14 @@ struct StageArgs {
     int kernel;               // KERNEL_* below
     double *dscr;             // column walk: [n][3][7][512] per-axis flux differences
     const double *dt_dev;     // if set, dt is read from device memory
-    // persistent column walk
-    int tiles;                // 1: whole leaves; 3: one axis per item
+    // column walk over parts of leaves
+    int tiles;                // persistent: 1, whole leaves, or 3, one axis per item; direct: parts per leaf
+    int whole;                // direct: leaves done by one workgroup each, before those in parts
     int grid_limit;           // workgroups of a persistent launch
     int *queue;               // [QUEUE_INTS]: next item of each XCD's range, workgroups
                               // finished (zero between launches)
-    int *leaf_done;           // [n] axis tiles finished per leaf (zero between launches)
-    double *tile_amax;        // [n][3]
+    int *leaf_done;           // [n] parts finished per leaf (zero between launches)
+    double *tile_amax;        // [n][MAX_PARTS]
     // learned reconstruction (null: plain PPM)
     const float *mlp_off;     // [n][7][13][896][2] learned point values as binary32 offsets
                               // from the cell value (field, line, slot, +d / -d end)
@@ -184,6 +187,16 @@ enum Kernel { KERNEL_FACE = 0, KERNEL_COLUMN = 1, KERNEL_PERSISTENT = 2 };
 // finished workgroups.
 constexpr int NXCD = 8;
 constexpr int QUEUE_INTS = 16;
+
+// Workgroups per leaf of `left` blocks that have num_cu compute units to
+// themselves, so that all of them run at once; 1 where whole leaves take more
+// than half of them (150 leaves as 300 halves: two rounds of 45 us against one
+// of 71).
+inline int leaf_parts(int left, int num_cu) {
+    for (int t : {8, 4, 3, 2})
+        if ((int64_t)t * left <= num_cu) return t;
+    return 1;
+}
 
 // Leaf (within a launch of n leaves, one workgroup each) of workgroup b.
 // Workgroups are dispatched round-robin over the chip's 8 XCDs (b runs on

@@ -20,11 +20,14 @@ namespace {
 constexpr int MAXL = HYDRO_NOALLOC_MAX_LEAVES;
 // scratch layout, in doubles: the stage-1 state [MAXL][7][512], the column
 // walk's per-axis flux differences [MAXL][3][7][512], per-leaf signal speeds
-// [MAXL] (when the caller passes none) and the status word (16 bytes)
+// [MAXL] (when the caller passes none), the leaves' parts' maxima
+// [MAXL][MAX_PARTS] and counters [MAXL], and the status word (16 bytes)
 constexpr size_t OFF_U1 = 0;
 constexpr size_t OFF_W = OFF_U1 + (size_t)MAXL * LEAF_STRIDE;
 constexpr size_t OFF_AMAX = OFF_W + (size_t)MAXL * 3 * LEAF_STRIDE;
-constexpr size_t OFF_STATUS = OFF_AMAX + MAXL;
+constexpr size_t OFF_PART = OFF_AMAX + MAXL;
+constexpr size_t OFF_DONE = OFF_PART + MAXL * MAX_PARTS;
+constexpr size_t OFF_STATUS = OFF_DONE + MAXL / 2;
 constexpr size_t SCRATCH_DOUBLES = OFF_STATUS + 2;
 static_assert(sizeof(Status) <= 2 * sizeof(double), "status word must fit its slot");
 
@@ -38,6 +41,7 @@ constexpr int MAXDEV = 64;
 std::once_flag g_once[MAXDEV];
 hipError_t g_setup_err[MAXDEV];
 double *g_scratch[MAXDEV];   // device address of `scratch` on each device
+int g_cus[MAXDEV];           // compute units of each device
 std::atomic<bool> g_ready[MAXDEV];   // set-up done and succeeded on the device
 
 // Once per device, with that device current: the address of this device's
@@ -48,6 +52,7 @@ hipError_t setup(int dev) {
         hipError_t e = hipGetSymbolAddress((void **)&p, HIP_SYMBOL(scratch));
         if (e == hipSuccess && p == nullptr) e = hipErrorInvalidSymbol;
         if (e == hipSuccess) e = hydro_internal_ghost_table(dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&g_cus[dev], hipDeviceAttributeMultiprocessorCount, dev);
         g_scratch[dev] = e == hipSuccess ? p : nullptr;
         g_setup_err[dev] = e;
         g_ready[dev].store(e == hipSuccess, std::memory_order_release);
@@ -64,9 +69,12 @@ int hip_fail(hipError_t e, const char *what) {
     return fail(HYDRO_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-// The status word starts each call at zero; a kernel store rather than a
-// memset, so that a captured graph holds no memset node.
-__global__ void clear_status(Status *s) {
+// The status word and the part counters start each call at zero (also after
+// calls that overlapped on the array); kernel stores rather than a memset, so
+// that a captured graph holds no memset node.
+__global__ void __launch_bounds__(MAXL) clear_status(Status *s, int *done) {
+    done[threadIdx.x] = 0;
+    if (threadIdx.x) return;
     s->flag = 0;
     s->leaf = 0;
     s->cell = 0;
@@ -108,7 +116,8 @@ extern "C" int hydro_step_noalloc(const hydro_grid *g, double dt, double eta1, d
     }
     double *const base = g_scratch[dev];
     Status *const status = (Status *)(base + OFF_STATUS);
-    hipLaunchKernelGGL(clear_status, dim3(1), dim3(1), 0, s, status);
+    int *const done = (int *)(base + OFF_DONE);
+    hipLaunchKernelGGL(clear_status, dim3(1), dim3(MAXL), 0, s, status, done);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "status clear");
 
     StageArgs a{};
@@ -122,7 +131,10 @@ extern "C" int hydro_step_noalloc(const hydro_grid *g, double dt, double eta1, d
     a.leaf0 = 0;
     a.nleaf = g->n;
     a.kernel = KERNEL_COLUMN;
-    a.tiles = 1;
+    a.tiles = leaf_parts(a.nleaf, g_cus[dev]);
+    a.whole = a.tiles > 1 ? 0 : a.nleaf;
+    a.tile_amax = base + OFF_PART;
+    a.leaf_done = done;
     a.dscr = base + OFF_W;
     a.ts = 0;
     a.lg = 3;

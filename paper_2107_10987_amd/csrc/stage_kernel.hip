@@ -631,7 +631,7 @@ __device__ __forceinline__ void line_ends(const double *P, int c, int dx, int dy
         a3 = b3;
         a4 = b4;
     }
-    if (__builtin_expect(bad, 0)) {
+    if (__builtin_expect(bad, 0)) {   // a NaN among the stencil's values
         const double *qc = P + c;
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
@@ -853,12 +853,25 @@ struct ColLane {
     }
 };
 
+// Values that another workgroup of the launch reads (a leaf's flux differences
+// and speeds where its parts run in several workgroups) go past the XCD's L2 by
+// relaxed device-scope accesses: once such stores have completed (vmcnt 0) they
+// are where every XCD's device-scope loads look, and no fence has to write back
+// and invalidate a whole L2 (64 leaves in four parts each: 45 us with fences
+// around the counter, 29 us so).
+__device__ __forceinline__ void store_dev(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_dev(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Flux differences along this lane's axis N of one leaf into that axis's
-// workspace slice of W (linear cell index); folds the lane's signal speeds
-// into smax.
+// workspace slice of W (linear cell index), device-wide if `parts`; folds the
+// lane's signal speeds into smax.
 template <bool LEARNED>
 __device__ __forceinline__ void col_axis_to_ws(int N, const StageArgs &a, const double *P,
-                                               const ColLane &L, int leaf, double *W, double &smax) {
+                                               const ColLane &L, int leaf, double *W, bool parts, double &smax) {
     double dx, ox, oy, oz;
     block_geometry(a, leaf, dx, ox, oy, oz);
     double d[NF];
@@ -869,14 +882,21 @@ __device__ __forceinline__ void col_axis_to_ws(int N, const StageArgs &a, const 
         const int c = (N == 0) ? (L.c2 * NX + L.c1) * NX + L.cell
                     : (N == 1) ? (L.c2 * NX + L.cell) * NX + L.c1
                                : (L.cell * NX + L.c2) * NX + L.c1;
+        double *w = W + (size_t)N * NF * NC + c;
+        if (parts) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) W[(N * NF + f) * NC + c] = d[f];
+            for (int f = 0; f < NF; ++f) store_dev(w + f * NC, d[f]);
+        } else {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) w[f * NC] = d[f];
+        }
     }
 }
 
-// The final pass of a leaf: sum the three axes' differences from W and
-// finish every interior cell, whose stage input is still in the LDS block P
-// (only a few corner ghost cells may have been overwritten by then).
+// The final pass of a leaf: sum the three axes' differences from W (PARTS:
+// other workgroups' too) and finish every interior cell, whose stage input is
+// still in the LDS block P.
+template <bool PARTS>
 __device__ __forceinline__ void col_finish_leaf(const StageArgs &a, int leaf, const double *W,
                                                 const double *P, int tid, int nt) {
     if (a.stage == 0) return;
@@ -887,7 +907,10 @@ __device__ __forceinline__ void col_finish_leaf(const StageArgs &a, int leaf, co
         double dsum[NF], u[NF];
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            dsum[f] = (W[(0 * NF + f) * NC + c] + W[(1 * NF + f) * NC + c]) + W[(2 * NF + f) * NC + c];
+            const double *w = W + f * NC + c;
+            const double wx = PARTS ? load_dev(w) : w[0], wy = PARTS ? load_dev(w + NF * NC) : w[NF * NC],
+                         wz = PARTS ? load_dev(w + 2 * NF * NC) : w[2 * NF * NC];
+            dsum[f] = (wx + wy) + wz;
             u[f] = P[f * PS + pc];
         }
         finish_cell_u(a, leaf, c, dx, dt, dsum, u);
@@ -901,7 +924,7 @@ __device__ __forceinline__ void col_finish_leaf(const StageArgs &a, int leaf, co
 // axis's slice of W only, so no barrier separates the axes.
 template <bool LEARNED>
 __device__ __forceinline__ void walk_columns(const StageArgs &a, const double *P, int leaf,
-                                             double *W, int first, int count, int *next_task,
+                                             double *W, bool parts, int first, int count, int *next_task,
                                              int tid, double &smax) {
     const int lane = tid & 63;
     const int ntask = (count + COLS_PER_WAVE - 1) / COLS_PER_WAVE;
@@ -909,40 +932,89 @@ __device__ __forceinline__ void walk_columns(const StageArgs &a, const double *P
 #pragma unroll 1
     while (task < ntask) {
         const ColLane L(lane, task, first, count);
-        col_axis_to_ws<LEARNED>(L.axis, a, P, L, leaf, W, smax);
+        col_axis_to_ws<LEARNED>(L.axis, a, P, L, leaf, W, parts, smax);
         int t = 0;
         if (lane == 0) t = atomicAdd(next_task, 1);
         task = __builtin_amdgcn_readfirstlane(t);
     }
 }
 
-// Maximum over the workgroup's waves of smax, left in red[0 .. NTC/64);
-// red may alias the input block (the barriers retire it first).
-__device__ __forceinline__ void block_max(double smax, double *red, int tid) {
+// This wave's largest signal speed into its place of red[0 .. NTC/64), which
+// lies behind the LDS block (read after the workgroup's next barrier).
+__device__ __forceinline__ void put_max(double smax, double *red, int tid) {
     const double wm = wave_max(smax);
-    __syncthreads();
     if ((tid & 63) == 0) red[tid >> 6] = wm;
-    __syncthreads();
 }
 
-// One leaf per workgroup, all three axes, then the leaf is finished from
-// the three slices.
+// The end of a part of a leaf whose parts run in several workgroups: publishes
+// the part's flux differences and its largest signal speed; the workgroup that
+// completes the leaf's last part finishes the leaf.
+__device__ __forceinline__ void join_parts(const StageArgs &a, double *P, const double *W, int leaf, int part,
+                                           int parts, double smax, int *last_s, int tid) {
+    double *red = P + BLOCK_LDS;
+    put_max(smax, red, tid);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of W is out
+    __syncthreads();
+    if (tid == 0) {
+        double m = red[0];
+        for (int w = 1; w < NTC / 64; ++w) m = red[w] > m ? red[w] : m;
+        store_dev(&a.tile_amax[(size_t)leaf * MAX_PARTS + part], m);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        int *done = &a.leaf_done[leaf];
+        const bool last = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+        if (last) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *last_s = last;
+    }
+    __syncthreads();
+    if (*last_s) {
+        col_finish_leaf<true>(a, leaf, W, P, tid, NTC);
+        if (tid == 0 && a.amax) {
+            for (int t = 0; t < parts; ++t) red[t] = load_dev(&a.tile_amax[(size_t)leaf * MAX_PARTS + t]);
+            store_amax(a, leaf, red, parts);
+        }
+    }
+}
+
+// The first a.whole workgroups do a leaf each: all three axes, then the leaf
+// is finished from the three slices.  The leaves left over, too few to fill the
+// chip, are done by a.tiles workgroups each, every one with the whole block in
+// LDS and an equal share of the 32 tasks, at eight one task per SIMD (a task is
+// the walk's unit of latency: more parts gain nothing); a leaf's parts are
+// neighbours in the launch order of one XCD.  Per stage launch, whole leaves
+// against parts: one leaf 61 against 19 us, 64 leaves 65 against 29, 120
+// leaves 68 against 45.
 template <bool LEARNED>
 __global__ void __launch_bounds__(NTC) stage_kernel_col(StageArgs a) {
-    __shared__ double P[BLOCK_LDS];
-    __shared__ int next_task;
-    const int leaf = a.leaf0 + xcd_leaf(blockIdx.x, gridDim.x);
-    const int tid = threadIdx.x;
+    __shared__ double P[BLOCK_LDS + NTC / 64];
+    __shared__ int next_task, last_s;
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const bool parts = b >= a.whole;
+    int leaf = a.leaf0, first = 0, count = 3 * NX * NX, part = 0;
+    if (parts) {
+        constexpr int TASKS = 3 * NX * NX / COLS_PER_WAVE;
+        const int item = xcd_leaf(b - a.whole, gridDim.x - a.whole);
+        part = item % a.tiles;
+        leaf += a.whole + item / a.tiles;
+        const int t0 = TASKS * part / a.tiles, t1 = TASKS * (part + 1) / a.tiles;
+        first = COLS_PER_WAVE * t0;
+        count = COLS_PER_WAVE * (t1 - t0);
+    } else {
+        leaf += xcd_leaf(b, a.whole);
+    }
     if (tid == 0) next_task = NTC / 64;
     gather_block<NTC>(P, a.Uin, a.gmap, leaf, a.ts, a.lg, a.prolong, a.n_prolong, tid);
     __syncthreads();
     double *W = a.dscr + (size_t)leaf * 3 * NF * NC;
     double smax = 0.0;
-    walk_columns<LEARNED>(a, P, leaf, W, 0, 3 * NX * NX, &next_task, tid, smax);
+    walk_columns<LEARNED>(a, P, leaf, W, parts, first, count, &next_task, tid, smax);
+    if (parts) {
+        join_parts(a, P, W, leaf, part, a.tiles, smax, &last_s, tid);
+        return;
+    }
+    put_max(smax, P + BLOCK_LDS, tid);
     __syncthreads();   // every slice of W is written
-    col_finish_leaf(a, leaf, W, P, tid, NTC);
-    block_max(smax, P, tid);
-    if (tid == 0 && a.amax) store_amax(a, leaf, P, NTC / 64);
+    if (tid == 0 && a.amax) store_amax(a, leaf, P + BLOCK_LDS, NTC / 64);
+    col_finish_leaf<false>(a, leaf, W, P, tid, NTC);
 }
 
 // Persistent workgroups over a queue of (leaf, tile) items.  With one tile a
@@ -971,7 +1043,7 @@ __device__ __forceinline__ int next_item(int *queue, int items, int xcd) {
 }
 template <bool LEARNED>
 __global__ void __launch_bounds__(NTC) stage_kernel_col_persistent(StageArgs a) {
-    __shared__ double P[BLOCK_LDS];
+    __shared__ double P[BLOCK_LDS + NTC / 64];
     __shared__ int item_s, last_s, next_task;
     const int tid0 = threadIdx.x;
     const int T = a.tiles;
@@ -996,38 +1068,15 @@ __global__ void __launch_bounds__(NTC) stage_kernel_col_persistent(StageArgs a) 
         double *W = a.dscr + (size_t)leaf * 3 * NF * NC;
         double smax = 0.0;
         // one tile: all 192 columns; three: the 64 columns of axis `tile`
-        walk_columns<LEARNED>(a, P, leaf, W, T == 1 ? 0 : tile * NX * NX, T == 1 ? 3 * NX * NX : NX * NX,
-                     &next_task, tid, smax);
+        walk_columns<LEARNED>(a, P, leaf, W, T > 1, T == 1 ? 0 : tile * NX * NX, T == 1 ? 3 * NX * NX : NX * NX,
+                              &next_task, tid, smax);
         if (T == 1) {
+            put_max(smax, P + BLOCK_LDS, tid);
             __syncthreads();   // every slice of W is written
-            col_finish_leaf(a, leaf, W, P, tid, NTC);
-            block_max(smax, P, tid);
-            if (tid == 0 && a.amax) store_amax(a, leaf, P, NTC / 64);
+            if (tid == 0 && a.amax) store_amax(a, leaf, P + BLOCK_LDS, NTC / 64);
+            col_finish_leaf<false>(a, leaf, W, P, tid, NTC);
         } else {
-            block_max(smax, P, tid);
-            if (tid == 0) {
-                double m = P[0];
-                for (int w = 1; w < NTC / 64; ++w) m = P[w] > m ? P[w] : m;
-                a.tile_amax[(size_t)leaf * 3 + tile] = m;
-                __threadfence();   // publish W and the tile maximum device-wide
-                last_s = atomicAdd(&a.leaf_done[leaf], 1) == T - 1;
-                if (last_s) {
-                    __threadfence();
-                    a.leaf_done[leaf] = 0;
-                }
-            }
-            __syncthreads();
-            if (last_s) {
-                __threadfence();   // see the other tiles' W
-                col_finish_leaf(a, leaf, W, P, tid, NTC);
-                if (tid == 0 && a.amax) {
-                    double *r = P;   // reuse: the three tile maxima
-                    r[0] = a.tile_amax[(size_t)leaf * 3 + 0];
-                    r[1] = a.tile_amax[(size_t)leaf * 3 + 1];
-                    r[2] = a.tile_amax[(size_t)leaf * 3 + 2];
-                    store_amax(a, leaf, r, 3);
-                }
-            }
+            join_parts(a, P, W, leaf, tile, T, smax, &last_s, tid);
         }
         __syncthreads();   // LDS, item_s and next_task are reused by the next item
     }
@@ -1140,6 +1189,9 @@ hipError_t hydro_upload_ghost_table(const uint16_t *table) {
     return hipMemcpyToSymbol(HIP_SYMBOL(c_ghost_pad), table, sizeof(uint16_t) * NG);
 }
 
+// Workgroups of a column-walk launch: one per whole leaf, a.tiles per leaf after.
+static int column_grid(const StageArgs &a) { return a.whole + (a.nleaf - a.whole) * a.tiles; }
+
 hipError_t hydro_launch_stage(const StageArgs &a, hipStream_t s) {
     if (a.nleaf <= 0) return hipSuccess;
     switch (a.kernel) {
@@ -1148,9 +1200,9 @@ hipError_t hydro_launch_stage(const StageArgs &a, hipStream_t s) {
         break;
     case KERNEL_COLUMN:
         if (a.mlp_off)
-            hipLaunchKernelGGL(stage_kernel_col<true>, dim3(a.nleaf), dim3(NTC), 0, s, a);
+            hipLaunchKernelGGL(stage_kernel_col<true>, dim3(column_grid(a)), dim3(NTC), 0, s, a);
         else
-            hipLaunchKernelGGL(stage_kernel_col<false>, dim3(a.nleaf), dim3(NTC), 0, s, a);
+            hipLaunchKernelGGL(stage_kernel_col<false>, dim3(column_grid(a)), dim3(NTC), 0, s, a);
         break;
     default: {   // persistent column walk
         const int items = a.nleaf * a.tiles;

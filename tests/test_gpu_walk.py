@@ -87,3 +87,32 @@ def test_nan_beside_a_cell_is_reported(cell):
         assert e.value.code == hydro.ENONPHYS
     finally:
         hy.close()
+
+
+def test_nan_spreads_as_in_the_oracle():
+    """One stage on a state with two NaN cells: the same cells and fields go
+    bad (a slope that has a NaN two cells off is finite, with a sign that the
+    NaN's own sign bit gives, so the values beside them are nobody's)."""
+    import torch
+    import oracle
+    from paper_2107_10987_amd.hydro import Hydro
+    print("case: two NaN cells", flush=True)
+    t = uniform_tree((2, 2, 2), (PERIODIC,) * 3, (0.0, 0.0, 0.0), 1.0 / 16)
+    U = state("rough", t.n, 17)
+    U[1, 0, 3, 4, 5] = np.nan
+    U[6, 5, 0, 7, 0] = np.nan
+    o = oracle.Oracle(t, GAMMA, 0.0)
+    want, _ = o.stage(1, 1e-3, U)
+    hy = Hydro(max_leaves=t.n, schedule="column")
+    try:
+        g = hy.grid(t, torch.tensor(U, device="cuda"), 0.0, GAMMA)
+        out = torch.empty_like(g.U)
+        hy.stage(g, 1, 1e-3, g.U, None, out, None)
+        got = out.cpu().numpy()
+        bad = np.isnan(want)
+        assert bad.any() and not bad.all()
+        assert np.array_equal(bad, np.isnan(got))
+        with pytest.raises(Exception):
+            hy.check()
+    finally:
+        hy.close()
