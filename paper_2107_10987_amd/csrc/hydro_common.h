@@ -111,22 +111,34 @@ __device__ __forceinline__ size_t src_offset(int s, int lg) {
 constexpr int PROLONG_BASE = 1 << 30;
 constexpr int PROLONG_ROW = 8;
 
-// Field f (fields fs = E^3 apart) of a copy or mean entry.
-__device__ __forceinline__ double src_value(const double *U, int s, int f, int lg) {
-    const size_t fs = (size_t)1 << (3 * lg);
-    if (s >= 0) return U[src_offset(s, lg) + f * fs];
-    const double *qf = U + src_offset(-s - 1, lg) + f * fs;
+// Mean of the 2x2x2 cells whose lowest is at q, summed in z, y, x order.
+__device__ __forceinline__ double mean_value(const double *q, int lg) {
     const int E = 1 << lg, E2 = E * E;
     double acc = 0.0;
-    acc = acc + qf[0];
-    acc = acc + qf[1];
-    acc = acc + qf[E];
-    acc = acc + qf[E + 1];
-    acc = acc + qf[E2];
-    acc = acc + qf[E2 + 1];
-    acc = acc + qf[E2 + E];
-    acc = acc + qf[E2 + E + 1];
+    acc = acc + q[0];
+    acc = acc + q[1];
+    acc = acc + q[E];
+    acc = acc + q[E + 1];
+    acc = acc + q[E2];
+    acc = acc + q[E2 + 1];
+    acc = acc + q[E2 + E];
+    acc = acc + q[E2 + E + 1];
     return acc * 0.125;
+}
+
+// All fields (fs = E^3 apart) of a copy or mean entry.  A gather waits on
+// memory, not on arithmetic: the fields' loads are issued together, so an entry
+// costs one latency and not seven.
+__device__ __forceinline__ void src_values(const double *U, int s, int lg, double v[NF]) {
+    const size_t fs = (size_t)1 << (3 * lg);
+    const double *q = U + src_offset(s >= 0 ? s : -s - 1, lg);
+    if (s >= 0) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f] = q[f * fs];
+    } else {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f] = mean_value(q + f * fs, lg);
+    }
 }
 
 __device__ __forceinline__ double minmod2(double a, double b) {
@@ -134,29 +146,39 @@ __device__ __forceinline__ double minmod2(double a, double b) {
     return fabs(a) <= fabs(b) ? a : b;
 }
 
-// Linear-limited prolongation of field f from a table row: U_C plus, axis by
-// axis in x, y, z order, (+-1/4) minmod(U_{C+e} - U_C, U_C - U_{C-e}).
-__device__ __forceinline__ double prolong_value(const double *U, const int32_t *row, int f, int lg) {
-    const double uc = src_value(U, row[0], f, lg);
-    double v = uc;
+// Linear-limited prolongation of all fields from a table row: U_C plus, axis
+// by axis in x, y, z order, (+-1/4) minmod(U_{C+e} - U_C, U_C - U_{C-e}).
+__device__ __forceinline__ void prolong_values(const double *U, const int32_t *row, int lg, double v[NF]) {
+    int r[PROLONG_ROW];
+#pragma unroll
+    for (int k = 0; k < PROLONG_ROW; ++k) r[k] = row[k];
+    double uc[NF];
+    src_values(U, r[0], lg, uc);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) v[f] = uc[f];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double um = src_value(U, row[1 + 2 * a], f, lg);
-        const double up = src_value(U, row[2 + 2 * a], f, lg);
-        const double frac = ((row[7] >> a) & 1) ? 0.25 : -0.25;
-        v = v + frac * minmod2(up - uc, uc - um);
+        double um[NF], up[NF];
+        src_values(U, r[1 + 2 * a], lg, um);
+        src_values(U, r[2 + 2 * a], lg, up);
+        const double frac = ((r[7] >> a) & 1) ? 0.25 : -0.25;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f] = v[f] + frac * minmod2(up[f] - uc[f], uc[f] - um[f]);
     }
-    return v;
 }
 
-// Field f of whatever a ghost-map entry names; an out-of-range prolongation
+// All fields of whatever a ghost-map entry names; an out-of-range prolongation
 // row (a map used with the wrong table) gives NaN, which the stage reports.
-__device__ __forceinline__ double ghost_value(const double *U, int s, int f, int lg, const int32_t *prolong,
-                                              int n_prolong) {
-    if (s >= -PROLONG_BASE) return src_value(U, s, f, lg);
+__device__ __forceinline__ void ghost_values(const double *U, int s, int lg, const int32_t *prolong,
+                                             int n_prolong, double v[NF]) {
+    if (s >= -PROLONG_BASE) return src_values(U, s, lg, v);
     const int r = -s - PROLONG_BASE - 1;
-    if (!prolong || r >= n_prolong) return __builtin_nan("");
-    return prolong_value(U, prolong + (size_t)r * PROLONG_ROW, f, lg);
+    if (!prolong || r >= n_prolong) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f] = __builtin_nan("");
+        return;
+    }
+    prolong_values(U, prolong + (size_t)r * PROLONG_ROW, lg, v);
 }
 
 // Boundary faces of a leaf: f = 2 axis + side (side 1 = +axis); the 64 face

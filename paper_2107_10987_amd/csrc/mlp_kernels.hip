@@ -509,9 +509,10 @@ __global__ void __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(7)
                 for (int ff = 0; ff < NF; ++ff) box[ff][c] = p[ff * fs];
             } else {
                 const int src = gm[c_pad_ghost[((z + GW) * PB + (y + GW)) * PB + (x + GW)]];
-#pragma unroll 1
-                for (int ff = 0; ff < NF; ++ff)
-                    box[ff][c] = ghost_value(m.U, src, ff, m.lg, m.prolong, m.n_prolong);
+                double gs[NF];
+                ghost_values(m.U, src, m.lg, m.prolong, m.n_prolong, gs);
+#pragma unroll
+                for (int ff = 0; ff < NF; ++ff) box[ff][c] = gs[ff];
             }
         }
     }

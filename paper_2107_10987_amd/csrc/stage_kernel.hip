@@ -285,6 +285,8 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
+typedef __attribute__((address_space(3))) double *lds_ptr;
+
 // Ghost-padded 14^3 block of block b into LDS (NTH threads cooperate): its
 // 8^3 cells from U, its ghost cells through the ghost map (a copy, or the mean
 // of the 2x2x2 cells of a finer leaf, summed in z, y, x order, or a
@@ -293,8 +295,12 @@ __device__ __forceinline__ double wave_max(double v) {
 // their padded positions), then the copied ghost values, all into registers
 // before any LDS store, so that each thread waits on memory about twice
 // rather than once per ghost cell.  Threads past the end of a range load and
-// store the last element again (the same value to the same place).
-template <int NTH>
+// store the last element again (the same value to the same place).  PROLONG:
+// the grid has prolongation rows (without, a row is NaN); the thirty values an
+// entry then has in flight would cost the plain walk's kernel its registers
+// (0.7% of a step of the binary), and one field after the other, each waiting on
+// memory, they cost a 664-leaf star a fifth of its step (1.79 against 1.45 ms).
+template <int NTH, bool PROLONG>
 __device__ __forceinline__ void gather_block(double *P, const double *U, const int32_t *gm, int b,
                                              int ts, int lg, const int32_t *prolong, int n_prolong,
                                              int tid) {
@@ -319,7 +325,6 @@ __device__ __forceinline__ void gather_block(double *P, const double *U, const i
     }
     // copied ghost values (the common case) straight into registers; means
     // and prolongation rows are formed after
-    const int E = 1 << lg, E2 = E * E;
     double gv[NGI][NF];
 #pragma unroll
     for (int i = 0; i < NGI; ++i) {
@@ -341,25 +346,15 @@ __device__ __forceinline__ void gather_block(double *P, const double *U, const i
         if (src >= 0) {
 #pragma unroll
             for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = gv[i][f];
-        } else if (src < -PROLONG_BASE) {
-#pragma unroll 1
-            for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = ghost_value(U, src, f, lg, prolong, n_prolong);
+        } else if (PROLONG || src < -PROLONG_BASE) {
+            double gs[NF];
+            ghost_values(U, src, lg, PROLONG ? prolong : nullptr, n_prolong, gs);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = gs[f];
         } else {
             const double *q = U + src_offset(-src - 1, lg);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const double *qf = q + f * fs;
-                double acc = 0.0;
-                acc = acc + qf[0];
-                acc = acc + qf[1];
-                acc = acc + qf[E];
-                acc = acc + qf[E + 1];
-                acc = acc + qf[E2];
-                acc = acc + qf[E2 + 1];
-                acc = acc + qf[E2 + E];
-                acc = acc + qf[E2 + E + 1];
-                P[f * PS + pads[i]] = acc * 0.125;
-            }
+            for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = mean_value(q + f * fs, lg);
         }
     }
 }
@@ -479,7 +474,7 @@ __global__ void __launch_bounds__(NT) stage_kernel(StageArgs a) {
     const int leaf = a.leaf0 + xcd_leaf(blockIdx.x, gridDim.x);
     const int tid = threadIdx.x;
 
-    gather_block<NT>(P, a.Uin, a.gmap, leaf, a.ts, a.lg, a.prolong, a.n_prolong, tid);
+    gather_block<NT, true>(P, a.Uin, a.gmap, leaf, a.ts, a.lg, a.prolong, a.n_prolong, tid);
     __syncthreads();
 
     double dx, org[3];
@@ -601,8 +596,7 @@ __device__ __forceinline__ void line_ends(const double *P, int c, int dx, int dy
     // reached by the loads' immediate offsets (four fields each) instead of
     // the strides being added up again for every field
     const int st = dx * SX_ + dy * SY_ + dz * SZ_;
-    typedef const __attribute__((address_space(3))) double *lds;
-    lds p0 = (lds)(P + c) - 2 * st, p1 = p0 + st, p2 = p1 + st, p3 = p2 + st, p4 = p3 + st;
+    lds_ptr p0 = (lds_ptr)(P + c) - 2 * st, p1 = p0 + st, p2 = p1 + st, p3 = p2 + st, p4 = p3 + st;
     asm("" : "+v"(p0), "+v"(p1), "+v"(p2), "+v"(p3), "+v"(p4));
     double a0 = *p0, a1 = *p1, a2 = *p2, a3 = *p3, a4 = *p4;
 #pragma unroll
@@ -983,7 +977,7 @@ __device__ __forceinline__ void join_parts(const StageArgs &a, double *P, const 
 // neighbours in the launch order of one XCD.  Per stage launch, whole leaves
 // against parts: one leaf 61 against 19 us, 64 leaves 65 against 29, 120
 // leaves 68 against 45.
-template <bool LEARNED>
+template <bool LEARNED, bool PROLONG>
 __global__ void __launch_bounds__(NTC) stage_kernel_col(StageArgs a) {
     __shared__ double P[BLOCK_LDS + NTC / 64];
     __shared__ int next_task, last_s;
@@ -1002,7 +996,7 @@ __global__ void __launch_bounds__(NTC) stage_kernel_col(StageArgs a) {
         leaf += xcd_leaf(b, a.whole);
     }
     if (tid == 0) next_task = NTC / 64;
-    gather_block<NTC>(P, a.Uin, a.gmap, leaf, a.ts, a.lg, a.prolong, a.n_prolong, tid);
+    gather_block<NTC, PROLONG>(P, a.Uin, a.gmap, leaf, a.ts, a.lg, a.prolong, a.n_prolong, tid);
     __syncthreads();
     double *W = a.dscr + (size_t)leaf * 3 * NF * NC;
     double smax = 0.0;
@@ -1041,7 +1035,7 @@ __device__ __forceinline__ int next_item(int *queue, int items, int xcd) {
     }
     return items;
 }
-template <bool LEARNED>
+template <bool LEARNED, bool PROLONG>
 __global__ void __launch_bounds__(NTC) stage_kernel_col_persistent(StageArgs a) {
     __shared__ double P[BLOCK_LDS + NTC / 64];
     __shared__ int item_s, last_s, next_task;
@@ -1063,7 +1057,7 @@ __global__ void __launch_bounds__(NTC) stage_kernel_col_persistent(StageArgs a) 
         if (item >= items) break;
         const int leaf = a.leaf0 + item / T;
         const int tile = item - (item / T) * T;
-        gather_block<NTC>(P, a.Uin, a.gmap, leaf, a.ts, a.lg, a.prolong, a.n_prolong, tid);
+        gather_block<NTC, PROLONG>(P, a.Uin, a.gmap, leaf, a.ts, a.lg, a.prolong, a.n_prolong, tid);
         __syncthreads();
         double *W = a.dscr + (size_t)leaf * 3 * NF * NC;
         double smax = 0.0;
@@ -1168,7 +1162,7 @@ __global__ void __launch_bounds__(NT) reconstruct_kernel(const double *U, const 
                                                          double *out) {
     __shared__ double P[BLOCK_LDS];
     const int leaf = blockIdx.x;
-    gather_block<NT>(P, U, gm, leaf, 0, 3, prolong, n_prolong, threadIdx.x);
+    gather_block<NT, true>(P, U, gm, leaf, 0, 3, prolong, n_prolong, threadIdx.x);
     __syncthreads();
     double *o = out + (size_t)leaf * NF * NC * 26;
     for (int e = threadIdx.x; e < NC * 26; e += NT) {
@@ -1192,6 +1186,13 @@ hipError_t hydro_upload_ghost_table(const uint16_t *table) {
 // Workgroups of a column-walk launch: one per whole leaf, a.tiles per leaf after.
 static int column_grid(const StageArgs &a) { return a.whole + (a.nleaf - a.whole) * a.tiles; }
 
+// The instantiation for a launch: learned values or not, prolongation rows or not.
+typedef void (*StageKernel)(StageArgs);
+static StageKernel variant(const StageArgs &a, StageKernel plain, StageKernel plain_pro, StageKernel learned,
+                           StageKernel learned_pro) {
+    return a.mlp_off ? (a.prolong ? learned_pro : learned) : (a.prolong ? plain_pro : plain);
+}
+
 hipError_t hydro_launch_stage(const StageArgs &a, hipStream_t s) {
     if (a.nleaf <= 0) return hipSuccess;
     switch (a.kernel) {
@@ -1199,18 +1200,16 @@ hipError_t hydro_launch_stage(const StageArgs &a, hipStream_t s) {
         hipLaunchKernelGGL(stage_kernel, dim3(a.nleaf), dim3(NT), 0, s, a);
         break;
     case KERNEL_COLUMN:
-        if (a.mlp_off)
-            hipLaunchKernelGGL(stage_kernel_col<true>, dim3(column_grid(a)), dim3(NTC), 0, s, a);
-        else
-            hipLaunchKernelGGL(stage_kernel_col<false>, dim3(column_grid(a)), dim3(NTC), 0, s, a);
+        hipLaunchKernelGGL(variant(a, stage_kernel_col<false, false>, stage_kernel_col<false, true>,
+                                   stage_kernel_col<true, false>, stage_kernel_col<true, true>),
+                           dim3(column_grid(a)), dim3(NTC), 0, s, a);
         break;
     default: {   // persistent column walk
         const int items = a.nleaf * a.tiles;
         const int grid = items < a.grid_limit ? items : a.grid_limit;
-        if (a.mlp_off)
-            hipLaunchKernelGGL(stage_kernel_col_persistent<true>, dim3(grid), dim3(NTC), 0, s, a);
-        else
-            hipLaunchKernelGGL(stage_kernel_col_persistent<false>, dim3(grid), dim3(NTC), 0, s, a);
+        hipLaunchKernelGGL(variant(a, stage_kernel_col_persistent<false, false>, stage_kernel_col_persistent<false, true>,
+                                   stage_kernel_col_persistent<true, false>, stage_kernel_col_persistent<true, true>),
+                           dim3(grid), dim3(NTC), 0, s, a);
     }
     }
     return hipGetLastError();
@@ -1226,7 +1225,7 @@ __global__ void __launch_bounds__(NT) pairs_kernel(const double *U, const int32_
                                                    float *T, uint8_t *valid) {
     __shared__ double P[BLOCK_LDS];
     const int leaf = blockIdx.x;
-    gather_block<NT>(P, U, gm, leaf, 0, 3, prolong, n_prolong, threadIdx.x);
+    gather_block<NT, true>(P, U, gm, leaf, 0, 3, prolong, n_prolong, threadIdx.x);
     __syncthreads();
     for (int e = threadIdx.x; e < NC * NF; e += NT) {
         const int c = e / NF, f = e - (e / NF) * NF;
