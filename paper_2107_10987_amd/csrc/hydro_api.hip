@@ -14,6 +14,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <type_traits>
 #include <unordered_map>
 #include <vector>
 
@@ -474,34 +475,34 @@ hipError_t mlp_alloc(hydro_t *h, T **p, size_t count) {
     return e;
 }
 
-// Network parameters, Adam state and training workspace (always: a few MB),
-// plus the per-leaf inference outputs when the learned path is on.
+// Network parameters, Adam state and training workspace (always: one
+// allocation of at most 2.3 MB), plus the per-leaf inference outputs when the
+// learned path is on.
 hipError_t alloc_mlp(hydro_t *h, size_t nleaves) {
-    const size_t B = h->p.mlp_batch > 0 ? (size_t)h->p.mlp_batch : 4096;
-    h->mlp_batch = (int)B;
+    h->mlp_batch = h->p.mlp_batch > 0 ? h->p.mlp_batch : 4096;
     mlp::MlpTrain &t = h->mt;
-    hipError_t e = mlp_alloc(h, &t.par, mlp::NPAR);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.m, mlp::NPAR);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.v, mlp::NPAR);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.grad, mlp::NPAR);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.wb, mlp::WB_SIZE);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.wbT, mlp::WBT_SIZE);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.wbi, mlp::WBI_SIZE);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.bi, mlp::BI_SIZE);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.xb, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.a1, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.a2, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.dz1, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.dz2, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.z1, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.z2, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.dz1f, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.dz2f, B * 64);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.y, B * 32);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.dy, B * 32);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.loss_rows, B);
-    if (e == hipSuccess) e = mlp_alloc(h, &t.gpart, (size_t)mlp::WG_SLICES * mlp::NPAR);
-    if (e == hipSuccess) e = mlp_alloc(h, &h->fb_count, 1);
+    const size_t slices = std::min(((size_t)h->mlp_batch + 63) / 64, (size_t)mlp::WG_SLICES);
+    char *base = nullptr;
+    size_t end = 0;
+    auto place = [&](auto **p, size_t count) {   // nothing but sizes while base is null
+        *p = (std::remove_reference_t<decltype(*p)>)(base + end);
+        end += (count * sizeof(**p) + 255) & ~(size_t)255;
+    };
+    hipError_t e = hipSuccess;
+    for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
+        if (pass) e = mlp_alloc(h, &base, end);
+        if (e != hipSuccess) break;
+        end = 0;
+        place(&t.par, mlp::NPAR);
+        place(&t.m, mlp::NPAR);
+        place(&t.v, mlp::NPAR);
+        place(&t.wb, mlp::WB_SIZE);
+        place(&t.wbT, mlp::WBT_SIZE);
+        place(&t.wbi, mlp::WBI_SIZE);
+        place(&t.bi, mlp::BI_SIZE);
+        place(&h->fb_count, 1);
+        place(&t.gpart, std::max(slices * mlp::GP_STRIDE, (size_t)h->mlp_batch * mlp::OUT));
+    }
     if (e == hipSuccess && h->p.recon == 1) {
         e = mlp_alloc(h, &h->mlp_off, nleaves * mlp::NSLOT * NF * 26);
         if (e == hipSuccess) e = mlp_alloc(h, &h->mlp_ok, nleaves * mlp::NSLOT);
@@ -980,10 +981,13 @@ int hydro_mlp_forward(hydro_t *h, const float *X, int B, float *Y, void *stream)
     if (!h->mlp_loaded) return fail(h, HYDRO_EINVAL, "hydro_mlp_load first");
     if ((rc = set_device(h))) return rc;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = hydro_mlp_launch_forward(h->mt, X, B, s);
-    if (e == hipSuccess)
-        e = hipMemcpy2DAsync(Y, 26 * sizeof(float), h->mt.y, 32 * sizeof(float), 26 * sizeof(float), B,
-                             hipMemcpyDeviceToDevice, s);
+    // waves read and write rows in any order: outputs that overlap the inputs
+    // go through the gradient workspace
+    const bool apart = Y + (size_t)B * mlp::OUT <= X || X + (size_t)B * mlp::IN <= Y;
+    float *out = apart ? Y : h->mt.gpart;
+    hipError_t e = hydro_mlp_launch_forward(h->mt, X, B, out, s);
+    if (e == hipSuccess && !apart)
+        e = hipMemcpyAsync(Y, out, sizeof(float) * mlp::OUT * (size_t)B, hipMemcpyDeviceToDevice, s);
     return e == hipSuccess ? HYDRO_OK : hip_fail(h, e, "network forward");
 }
 
@@ -996,10 +1000,7 @@ int hydro_mlp_grad(hydro_t *h, const float *X, const float *T, int B, float *gra
     if (!h->mlp_loaded) return fail(h, HYDRO_EINVAL, "hydro_mlp_load first");
     if ((rc = set_device(h))) return rc;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = hydro_mlp_launch_forward(h->mt, X, B, s);
-    if (e == hipSuccess) e = hydro_mlp_launch_grad(h->mt, T, B, loss, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(grad, h->mt.grad, sizeof(float) * mlp::NPAR, hipMemcpyDeviceToDevice, s);
+    hipError_t e = hydro_mlp_launch_grad(h->mt, X, T, B, grad, loss, s);
     return e == hipSuccess ? HYDRO_OK : hip_fail(h, e, "network gradient");
 }
 
@@ -1016,10 +1017,7 @@ int hydro_mlp_train_step(hydro_t *h, const float *X, const float *T, int B, doub
     const double b1 = 0.9, b2 = 0.999;
     ++h->adam_t;
     const float c1 = (float)(1.0 - pow(b1, h->adam_t)), c2 = (float)(1.0 - pow(b2, h->adam_t));
-    hipError_t e = hydro_mlp_launch_forward(h->mt, X, B, s);
-    if (e == hipSuccess) e = hydro_mlp_launch_grad(h->mt, T, B, loss, s);
-    if (e == hipSuccess) e = hydro_mlp_launch_adam(h->mt, (float)lr, (float)b1, (float)b2, 1e-8f, c1, c2, s);
-    if (e == hipSuccess) e = hydro_mlp_launch_pack(h->mt, s);
+    hipError_t e = hydro_mlp_launch_step(h->mt, X, T, B, (float)lr, (float)b1, (float)b2, 1e-8f, c1, c2, loss, s);
     return e == hipSuccess ? HYDRO_OK : hip_fail(h, e, "network train step");
 }
 

@@ -20,8 +20,9 @@ constexpr int WB_W2T = 0, WB_W3T = 4096, WBT_SIZE = 8192;
 // one-hot input's weight folded in), b2, b3
 constexpr int NNB = 27;
 // weight-gradient reduction: 36 MFMA tiles (W3 2 x 4, W2 4 x 4, W1 4 x 3) per
-// batch slice
-constexpr int WG_TILES = 36, WG_SLICES = 16;
+// slice of the batch; at most WG_SLICES slices of GP_STRIDE sums (the
+// parameters' and the loss)
+constexpr int WG_TILES = 36, WG_SLICES = 64, GP_STRIDE = 8192;
 constexpr int WBI_SIZE = 8192;
 constexpr int BI_B1 = 0, BI_B2 = 448, BI_B3 = 512, BI_SIZE = 544;
 // cells whose reconstruction a leaf's fluxes need: 512 interior + 6 x 64
@@ -93,15 +94,11 @@ __device__ __forceinline__ void learned_limit(double qc, double nbR, double nbL,
 }
 
 struct MlpTrain {
-    float *par, *m, *v, *grad;          // [NPAR]
+    float *par, *m, *v;                 // [NPAR]
     uint16_t *wb, *wbT;                 // bf16 MFMA copies
     uint16_t *wbi;                      // [WBI_SIZE] inference image
     float *bi;                          // [BI_SIZE] inference biases
-    uint16_t *xb, *a1, *a2, *dz1, *dz2; // [B][64] bf16
-    float *z1, *z2, *dz1f, *dz2f;       // [B][64]
-    float *y, *dy;                      // [B][32]
-    float *loss_rows;                   // [B]
-    float *gpart;                       // [WG_SLICES][NPAR] per-slice gradients
+    float *gpart;                       // [WG_SLICES][GP_STRIDE] per-slice gradients
 };
 
 struct MlpInfer {
@@ -129,8 +126,8 @@ struct MlpInfer {
 hipError_t hydro_mlp_upload_pad_ghost(const int16_t *pad_ghost);
 hipError_t hydro_mlp_launch_infer(const hydro::mlp::MlpInfer &m, int nleaf, hipStream_t s);
 hipError_t hydro_mlp_launch_pack(const hydro::mlp::MlpTrain &t, hipStream_t s);
-hipError_t hydro_mlp_launch_forward(const hydro::mlp::MlpTrain &t, const float *X, int B, hipStream_t s);
-hipError_t hydro_mlp_launch_grad(const hydro::mlp::MlpTrain &t, const float *T, int B, float *loss,
-                                 hipStream_t s);
-hipError_t hydro_mlp_launch_adam(const hydro::mlp::MlpTrain &t, float lr, float b1, float b2, float eps,
-                                 float c1, float c2, hipStream_t s);
+hipError_t hydro_mlp_launch_forward(const hydro::mlp::MlpTrain &t, const float *X, int B, float *Y, hipStream_t s);
+hipError_t hydro_mlp_launch_grad(const hydro::mlp::MlpTrain &t, const float *X, const float *T, int B, float *grad,
+                                 float *loss, hipStream_t s);
+hipError_t hydro_mlp_launch_step(const hydro::mlp::MlpTrain &t, const float *X, const float *T, int B, float lr,
+                                 float b1, float b2, float eps, float c1, float c2, float *loss, hipStream_t s);

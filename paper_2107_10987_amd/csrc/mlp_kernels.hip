@@ -26,13 +26,12 @@ namespace {
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// Training kernels: LDS staging of a wave's 64 rows, bf16 rows of 64 padded to a 68-element
-// (136 B) stride, FP32 output rows of 32 padded to 34 (136 B).  Rows written
-// one per lane then fall in different banks, and the 8-byte MFMA operand
-// loads stay aligned.
+// Forward and training kernels: a wave holds 16 rows.  LDS staging of a wave's
+// bf16 rows of 64, padded to a 68-element (136 B) stride: rows written by
+// columns then fall in different banks, and the 8-byte MFMA operand loads stay
+// aligned.
 constexpr int LDA = 68;
-constexpr int LDY = 34;
-constexpr int STAGE_ELEMS = 64 * LDA;   // bf16 elements per wave
+constexpr int STAGE_ELEMS = 16 * LDA;   // bf16 elements per wave
 
 __device__ __forceinline__ v4f mfma(v4s a, v4s b, v4f c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -49,85 +48,114 @@ __device__ __forceinline__ float bf16_float(uint16_t b) { return __uint_as_float
 constexpr float GELU_C = 0.7978845608028654f;
 constexpr float GELU_A = 0.044715f;
 
-__device__ __forceinline__ float gelu(float z) {
-    return 0.5f * z * (1.0f + tanhf(GELU_C * (z + GELU_A * z * z * z)));
-}
-__device__ __forceinline__ float gelu_grad(float z) {
-    const float t = tanhf(GELU_C * (z + GELU_A * z * z * z));
+__device__ __forceinline__ float gelu_tanh(float z) { return tanhf(GELU_C * (z + GELU_A * z * z * z)); }
+__device__ __forceinline__ float gelu(float z, float t) { return 0.5f * z * (1.0f + t); }
+__device__ __forceinline__ float gelu_grad(float z, float t) {
     return 0.5f * (1.0f + t) + 0.5f * z * (1.0f - t * t) * GELU_C * (1.0f + 3.0f * GELU_A * z * z);
 }
 
-// One layer for a wave's 64 rows: Z[r][n] = sum_k A[r][k] W[n][k] + b[n],
-// A in LDS (bf16, row stride 64), W bf16 [NT*16][64] in global memory.
-// Results in D layout: z[mt][nt] holds rows 16 mt + 4q + i, column 16 nt + l%16.
-template <int NTILE>
-__device__ __forceinline__ void layer(const uint16_t *A, const uint16_t *W, int lane, v4f z[4][NTILE]) {
+// One layer for a wave's 16 rows: Z[r][n] = sum_k A[r][k] W[n][k], A in LDS
+// (bf16, row stride LDA), W bf16 [NTILE * 16][64] in global memory, k below
+// 16 KB (the rest of A is zero).  Results in D layout: z[nt] holds rows 4q + i,
+// column 16 nt + l % 16.
+template <int NTILE, int KB>
+__device__ __forceinline__ void layer(const uint16_t *A, const uint16_t *W, int lane, v4f z[NTILE]) {
     const int r = lane & 15, q = lane >> 4;
+    v4s b[KB][NTILE];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int nt = 0; nt < NTILE; ++nt) z[mt][nt] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int nt = 0; nt < NTILE; ++nt) b[kb][nt] = *(const v4s *)(W + (16 * nt + r) * 64 + 16 * kb + 4 * q);
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-        v4s b[NTILE];
+    for (int nt = 0; nt < NTILE; ++nt) z[nt] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int nt = 0; nt < NTILE; ++nt)
-            b[nt] = *(const v4s *)(W + (16 * nt + r) * 64 + 16 * kb + 4 * q);   // global, stride 64
+    for (int kb = 0; kb < KB; ++kb) {
+        const v4s a = *(const v4s *)(A + r * LDA + 16 * kb + 4 * q);
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const v4s a = *(const v4s *)(A + (16 * mt + r) * LDA + 16 * kb + 4 * q);
-#pragma unroll
-            for (int nt = 0; nt < NTILE; ++nt) z[mt][nt] = mfma(a, b[nt], z[mt][nt]);
-        }
+        for (int nt = 0; nt < NTILE; ++nt) z[nt] = mfma(a, b[kb][nt], z[nt]);
     }
 }
 
-// Bias, GELU and bfloat16 rounding of a hidden layer back into the staging
-// buffer S (rows x 64); optionally keeps z (FP32) and a (bf16) per row in
-// global memory for the backward pass.
-__device__ __forceinline__ void hidden_out(v4f z[4][4], const float *bias, uint16_t *S, int lane,
-                                           float *zsave, uint16_t *asave, int row0, int nrows) {
-    const int c = lane & 15, q = lane >> 4;
+// Four values of D-layout rows 4q .. 4q + 3 as bfloat16: rows of one column,
+// which is also how an MFMA operand holds them when the rows are contracted.
+__device__ __forceinline__ v4s pack4(const float v[4]) {
+    v4s r;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = 16 * mt + 4 * q + i, col = 16 * nt + c;
-                const float zz = z[mt][nt][i] + bias[col];
-                const uint16_t a = bf16_bits(gelu(zz));
-                S[row * LDA + col] = a;
-                if (zsave && row < nrows) {
-                    zsave[(size_t)(row0 + row) * 64 + col] = zz;
-                    asave[(size_t)(row0 + row) * 64 + col] = a;
-                }
-            }
+    for (int i = 0; i < 4; ++i) r[i] = (short)bf16_bits(v[i]);
+    return r;
 }
 
-// Forward pass of the 64 rows staged (as bf16 inputs) in S; the 26 outputs of
-// row r land in Y[r][0..25] (FP32, row stride LDY, aliasing S).
-__device__ __forceinline__ void forward64(uint16_t *S, const uint16_t *Wb, const float *par, int lane,
-                                          float *z1s, uint16_t *a1s, float *z2s, uint16_t *a2s, int row0,
-                                          int nrows) {
-    v4f z[4][4];
-    layer<4>(S, Wb + WB_W1, lane, z);
-    hidden_out(z, par + P_B1, S, lane, z1s, a1s, row0, nrows);
-    layer<4>(S, Wb + WB_W2, lane, z);
-    hidden_out(z, par + P_B2, S, lane, z2s, a2s, row0, nrows);
-    v4f y[4][2];
-    layer<2>(S, Wb + WB_W3, lane, y);
-    float *Y = (float *)S;
+// Column 16 nt + l % 16 of the wave's rows into the staging buffer.
+__device__ __forceinline__ void stage_col(uint16_t *S, int nt, int lane, v4s v) {
     const int c = lane & 15, q = lane >> 4;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int i = 0; i < 4; ++i) S[(4 * q + i) * LDA + 16 * nt + c] = (uint16_t)v[i];
+}
+
+// The staging buffer is private to its wave, whose LDS accesses are performed
+// in order: only the compiler has to keep them so.
+__device__ __forceinline__ void stage_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Forward pass of the 16 rows row0 .. of X [B][34] (float32; rows past nrows are
+// zero): z and tanh of the two hidden layers (D layout), their bf16
+// activations, and the output layer's columns in y (D layout, bias added).
+struct Forward {
+    v4f z1[4], z2[4], y[2];
+    float t1[4][4], t2[4][4];
+    v4s a1[4], a2[4];
+};
+__device__ __forceinline__ void forward16(const float *X, int row0, int nrows, const uint16_t *Wb, const float *par,
+                                          uint16_t *S, int lane, Forward &o) {
+    const int r = lane & 15, q = lane >> 4;
+    // this lane's operand of the first layer: row r, inputs 16 kb + 4q + i
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+    for (int kb = 0; kb < 3; ++kb) {
+        float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = 16 * mt + 4 * q + i, col = 16 * nt + c;
-                if (col < OUT) Y[row * LDY + col] = y[mt][nt][i] + par[P_B3 + col];
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int k = 16 * kb + 4 * q + i;
+            v[i] = (r < nrows && k < IN) ? X[(size_t)(row0 + r) * IN + k] : 0.f;
+        }
+        *(v4s *)(S + r * LDA + 16 * kb + 4 * q) = pack4(v);
+    }
+    stage_fence();
+    layer<4, 3>(S, Wb + WB_W1, lane, o.z1);
+    stage_fence();
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        float a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            o.z1[nt][i] += par[P_B1 + 16 * nt + r];
+            o.t1[nt][i] = gelu_tanh(o.z1[nt][i]);
+            a[i] = gelu(o.z1[nt][i], o.t1[nt][i]);
+        }
+        o.a1[nt] = pack4(a);
+        stage_col(S, nt, lane, o.a1[nt]);
+    }
+    stage_fence();
+    layer<4, 4>(S, Wb + WB_W2, lane, o.z2);
+    stage_fence();
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        float a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            o.z2[nt][i] += par[P_B2 + 16 * nt + r];
+            o.t2[nt][i] = gelu_tanh(o.z2[nt][i]);
+            a[i] = gelu(o.z2[nt][i], o.t2[nt][i]);
+        }
+        o.a2[nt] = pack4(a);
+        stage_col(S, nt, lane, o.a2[nt]);
+    }
+    stage_fence();
+    layer<2, 4>(S, Wb + WB_W3, lane, o.y);
+    stage_fence();
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (16 * nt + r < OUT) o.y[nt][i] += par[P_B3 + 16 * nt + r];
 }
 
 // GELU for inference: 0.5 z (1 + tanh u) = z / (1 + exp(-2u)),
@@ -145,169 +173,205 @@ __device__ __forceinline__ float gelu_fast(float z) {
 // Training
 // ---------------------------------------------------------------------------
 
-// Forward of B rows of X [B][34] (float32); keeps what the backward needs.
-__global__ void __launch_bounds__(256) mlp_train_forward(MlpTrain t, const float *X, int B) {
-    __shared__ uint16_t S[4][STAGE_ELEMS];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int row0 = (blockIdx.x * 4 + w) * 64;
-    if (row0 >= B) return;                        // wave-uniform
-    const int nrows = B - row0 < 64 ? B - row0 : 64;
-    uint16_t *s = S[w];
-    // row `lane`: inputs rounded to bf16, zero padding beyond 34 and beyond B
-    for (int k = 0; k < 64; ++k) {
-        const float v = (lane < nrows && k < IN) ? X[(size_t)(row0 + lane) * IN + k] : 0.f;
-        const uint16_t b = bf16_bits(v);
-        s[lane * LDA + k] = b;
-        if (lane < nrows) t.xb[(size_t)(row0 + lane) * 64 + k] = b;
-    }
-    forward64(s, t.wb, t.par, lane, t.z1, t.a1, t.z2, t.a2, row0, nrows);
-    const float *Y = (const float *)s;
-    if (lane < nrows)
-        for (int o = 0; o < OUT; ++o) t.y[(size_t)(row0 + lane) * 32 + o] = Y[lane * LDY + o];
-}
-
-// dY = 2 (y - T) / (B * 26); dZ2 = (dY W3) * gelu'(z2); dZ1 = (dZ2 W2) * gelu'(z1).
-// One wave per 64 rows; per-row loss partials.
-__global__ void __launch_bounds__(256) mlp_train_backward_rows(MlpTrain t, const float *T, int B) {
-    __shared__ uint16_t S[4][STAGE_ELEMS];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int row0 = (blockIdx.x * 4 + w) * 64;
-    if (row0 >= B) return;
-    const int nrows = B - row0 < 64 ? B - row0 : 64;
-    uint16_t *s = S[w];
-    const float scale = 2.0f / ((float)B * OUT);
-    float loss = 0.f;
-    for (int o = 0; o < 64; ++o) {
-        float d = 0.f;
-        if (lane < nrows && o < OUT) {
-            const float r = t.y[(size_t)(row0 + lane) * 32 + o] - T[(size_t)(row0 + lane) * OUT + o];
-            loss += r * r;
-            d = scale * r;
-            t.dy[(size_t)(row0 + lane) * 32 + o] = d;
-        }
-        s[lane * LDA + o] = bf16_bits(d);   // dY as the A operand (k = output index)
-    }
-    if (lane < nrows) t.loss_rows[row0 + lane] = loss;
-    // dA2[r][h] = sum_o dY[r][o] W3[o][h]: B operand[k = o][n = h] = W3[o][h] -> W3T copy
-    v4f z[4][4];
-    layer<4>(s, t.wbT + WB_W3T, lane, z);
-    const int c = lane & 15, q = lane >> 4;
-    // dZ2 = dA2 * gelu'(z2) -> bf16 into s (A operand of the next product) and global
-    for (int mt = 0; mt < 4; ++mt)
-        for (int nt = 0; nt < 4; ++nt)
-            for (int i = 0; i < 4; ++i) {
-                const int row = 16 * mt + 4 * q + i, col = 16 * nt + c;
-                float d = 0.f;
-                if (row < nrows) d = z[mt][nt][i] * gelu_grad(t.z2[(size_t)(row0 + row) * 64 + col]);
-                if (row < nrows) t.dz2f[(size_t)(row0 + row) * 64 + col] = d;
-                const uint16_t b = bf16_bits(d);
-                s[row * LDA + col] = b;
-                if (row < nrows) t.dz2[(size_t)(row0 + row) * 64 + col] = b;
-            }
-    layer<4>(s, t.wbT + WB_W2T, lane, z);
-    for (int mt = 0; mt < 4; ++mt)
-        for (int nt = 0; nt < 4; ++nt)
-            for (int i = 0; i < 4; ++i) {
-                const int row = 16 * mt + 4 * q + i, col = 16 * nt + c;
-                if (row < nrows) {
-                    const float d = z[mt][nt][i] * gelu_grad(t.z1[(size_t)(row0 + row) * 64 + col]);
-                    t.dz1f[(size_t)(row0 + row) * 64 + col] = d;
-                    t.dz1[(size_t)(row0 + row) * 64 + col] = bf16_bits(d);
-                }
-            }
-}
-
-// Weight and bias gradients, summed over the batch in a fixed order: the
-// batch is cut into WG_SLICES slices of whole 16-row blocks; workgroup
-// (slice, tile) reduces its slice for one 16 x 16 tile of one weight matrix on
-// MFMA (and, for the first tile of a row block, the bias sums) into the
-// slice's partial vector; mlp_grad_reduce then adds the slices in order.
-__global__ void __launch_bounds__(64) mlp_train_wgrad(MlpTrain t, int B) {
-    const int lane = threadIdx.x;
-    const int tile = blockIdx.x % WG_TILES, slice = blockIdx.x / WG_TILES;
-    const int per = (B + 16 * WG_SLICES - 1) / (16 * WG_SLICES) * 16;
-    const int r0 = slice * per, r1 = min(B, r0 + per);
-    float *gp = t.gpart + (size_t)slice * NPAR;
-    const uint16_t *dZ, *A;
-    int mt, nt, ldz, gofs, mrows, ncols;
-    if (tile < 8) {            // W3: dZ = dY (bf16 copy), A = a2
-        dZ = nullptr; A = t.a2; mt = tile / 4; nt = tile % 4; ldz = 32; gofs = P_W3; mrows = OUT; ncols = HID;
-    } else if (tile < 24) {    // W2: dZ = dZ2, A = a1
-        dZ = t.dz2; A = t.a1; mt = (tile - 8) / 4; nt = (tile - 8) % 4; ldz = 64; gofs = P_W2; mrows = HID; ncols = HID;
-    } else {                   // W1: dZ = dZ1, A = x
-        dZ = t.dz1; A = t.xb; mt = (tile - 24) / 3; nt = (tile - 24) % 3; ldz = 64; gofs = P_W1; mrows = HID; ncols = IN;
-    }
-    const int r = lane & 15, q = lane >> 4;
-    v4f acc = {0.f, 0.f, 0.f, 0.f};
-    for (int b0 = r0; b0 < r1; b0 += 16) {
-        // A operand [m][k = batch]: dZ[b0 + 4q + i][16 mt + r]
-        v4s a, bb;
+// Network outputs Y [B][26] of B rows of X [B][34], one wave per 16 rows: the
+// weights come from L2 into registers and nothing is kept, so a call is one
+// launch of as many waves as the batch has (64 rows per wave left a batch of
+// 1003 on 4 compute units, 60 us; now 8 us).
+__global__ void __launch_bounds__(64) mlp_forward(MlpTrain t, const float *X, int B, float *Y) {
+    __shared__ __attribute__((aligned(16))) uint16_t S[STAGE_ELEMS];
+    const int lane = threadIdx.x, r = lane & 15, q = lane >> 4;
+    const int row0 = blockIdx.x * 16;
+    Forward o;
+    forward16(X, row0, B - row0, t.wb, t.par, S, lane, o);
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int row = b0 + 4 * q + i;
-            uint16_t va = 0, vb = 0;
-            if (row < r1) {
-                const int m = 16 * mt + r, n = 16 * nt + r;
-                if (m < mrows) va = dZ ? dZ[(size_t)row * ldz + m] : bf16_bits(t.dy[(size_t)row * 32 + m]);
-                vb = A[(size_t)row * 64 + n];
+            const int row = row0 + 4 * q + i, col = 16 * nt + r;
+            if (row < B && col < OUT) Y[(size_t)row * OUT + col] = o.y[nt][i];
+        }
+}
+
+// Forward, backward and the partial weight gradients of groups of 64 rows, a
+// wave per 16 rows, in one pass: dY = 2 (y - T) / (B * 26);
+// dZ2 = (dY W3) * gelu'(z2); dZ1 = (dZ2 W2) * gelu'(z1).  Everything stays in
+// registers and LDS.  An MFMA result holds, per lane, four rows of a column,
+// which is an operand of the products dZ^T A over the rows: the waves lay
+// those operands down in LDS (44 KB) and each takes nine of the 36 gradient
+// tiles over the group's rows, and over the groups group, group + grid, ...;
+// the workgroup's sums go to its slice of gpart, where mlp_reduce adds the
+// slices in order (deterministic).  A batch of 4096 is 64 workgroups; its
+// 62 + 73 + 80 us in three kernels with the rows in memory between them take 20.
+constexpr int OP_DY = 0, OP_DZ2 = 2, OP_DZ1 = 6, OP_A2 = 10, OP_A1 = 14, OP_X = 18, OPS = 21;
+
+__global__ void __launch_bounds__(256) mlp_train_rows(MlpTrain t, const float *X, const float *T, int B) {
+    __shared__ __attribute__((aligned(16))) uint16_t stage[4][STAGE_ELEMS];
+    __shared__ v4s op[OPS][4][64];
+    __shared__ float red[4][160];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
+    uint16_t *S = stage[w];
+    const float scale = 2.0f / ((float)B * OUT);
+    v4f acc[WG_TILES / 4];
+#pragma unroll
+    for (int j = 0; j < WG_TILES / 4; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    float db1[4] = {0.f, 0.f, 0.f, 0.f}, db2[4] = {0.f, 0.f, 0.f, 0.f}, db3[2] = {0.f, 0.f}, loss = 0.f;
+    for (int g = blockIdx.x; 64 * g < B; g += gridDim.x) {
+        const int row0 = 64 * g + 16 * w, nrows = min(16, B - row0);   // nrows <= 0: an empty wave
+        const v4s zero = {0, 0, 0, 0};
+        Forward o;
+        forward16(X, row0, nrows, t.wb, t.par, S, lane, o);
+        // dY, its bias sums and the loss (columns 26..31 are zero)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            float d[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 4 * q + i, col = 16 * nt + r;
+                d[i] = 0.f;
+                if (row < nrows && col < OUT) {
+                    const float e = o.y[nt][i] - T[(size_t)(row0 + row) * OUT + col];
+                    loss += e * e;
+                    d[i] = scale * e;
+                }
+                db3[nt] += d[i];
             }
-            a[i] = (short)va;
-            bb[i] = (short)vb;
+            const v4s v = pack4(d);
+            stage_col(S, nt, lane, v);
+            op[OP_DY + nt][w][lane] = v;
         }
-        acc = mfma(a, bb, acc);
+        stage_fence();
+        // dA2[r][h] = sum_o dY[r][o] W3[o][h]
+        v4f z[4];
+        layer<4, 2>(S, t.wbT + WB_W3T, lane, z);
+        stage_fence();
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            float d[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                d[i] = 4 * q + i < nrows ? z[nt][i] * gelu_grad(o.z2[nt][i], o.t2[nt][i]) : 0.f;
+                db2[nt] += d[i];
+            }
+            const v4s v = pack4(d);
+            stage_col(S, nt, lane, v);
+            op[OP_DZ2 + nt][w][lane] = v;
+        }
+        stage_fence();
+        layer<4, 4>(S, t.wbT + WB_W2T, lane, z);
+        stage_fence();
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            float d[4];
+            v4s a1 = o.a1[nt], a2 = o.a2[nt];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool in = 4 * q + i < nrows;
+                d[i] = in ? z[nt][i] * gelu_grad(o.z1[nt][i], o.t1[nt][i]) : 0.f;
+                db1[nt] += d[i];
+                if (!in) a1[i] = a2[i] = 0;
+            }
+            op[OP_DZ1 + nt][w][lane] = pack4(d);
+            op[OP_A1 + nt][w][lane] = a1;
+            op[OP_A2 + nt][w][lane] = a2;
+        }
+#pragma unroll
+        for (int nt = 0; nt < 3; ++nt) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 4 * q + i, k = 16 * nt + r;
+                v[i] = (row < nrows && k < IN) ? X[(size_t)(row0 + row) * IN + k] : 0.f;
+            }
+            op[OP_X + nt][w][lane] = nrows > 0 ? pack4(v) : zero;
+        }
+        __syncthreads();
+        // tiles w, w + 4, ...: 0..7 W3 (2 x 4), 8..23 W2 (4 x 4), 24..35 W1 (4 x 3)
+#pragma unroll
+        for (int j = 0; j < WG_TILES / 4; ++j) {
+            const int tile = 4 * j + w;
+            const int oa = tile < 8 ? OP_DY + tile / 4 : (tile < 24 ? OP_DZ2 + (tile - 8) / 4 : OP_DZ1 + (tile - 24) / 3);
+            const int ob = tile < 8 ? OP_A2 + tile % 4 : (tile < 24 ? OP_A1 + tile % 4 : OP_X + (tile - 24) % 3);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[j] = mfma(op[oa][k][lane], op[ob][k][lane], acc[j]);
+        }
+        __syncthreads();   // the operands are replaced by the next group's
     }
-    for (int i = 0; i < 4; ++i) {
-        const int m = 16 * mt + 4 * q + i, n = 16 * nt + r;
-        if (m < mrows && n < ncols) gp[gofs + m * ncols + n] = acc[i];
-    }
-    // bias gradients: the first tile of each matrix's row block sums columns
-    if (nt == 0 && lane < 16) {
-        const int m = 16 * mt + lane;
-        if (m < mrows) {
-            float s = 0.f;
-            for (int b = r0; b < r1; ++b)
-                s += (tile < 8) ? t.dy[(size_t)b * 32 + m]
-                                : (tile < 24 ? t.dz2f[(size_t)b * 64 + m] : t.dz1f[(size_t)b * 64 + m]);
-            const int bofs = tile < 8 ? P_B3 : (tile < 24 ? P_B2 : P_B1);
-            gp[bofs + m] = s;
+    float *gp = t.gpart + (size_t)blockIdx.x * GP_STRIDE;
+#pragma unroll
+    for (int j = 0; j < WG_TILES / 4; ++j) {
+        const int tile = 4 * j + w;
+        const int mt = tile < 8 ? tile / 4 : (tile < 24 ? (tile - 8) / 4 : (tile - 24) / 3);
+        const int nt = tile < 24 ? tile % 4 : (tile - 24) % 3;
+        const int ofs = tile < 8 ? P_W3 : (tile < 24 ? P_W2 : P_W1);
+        const int rows = tile < 8 ? OUT : HID, cols = tile < 24 ? HID : IN;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int m = 16 * mt + 4 * q + i, n = 16 * nt + r;
+            if (m < rows && n < cols) gp[ofs + m * cols + n] = acc[j][i];
         }
     }
-}
-
-// grad = the slices' partial gradients added in slice order.
-__global__ void __launch_bounds__(256) mlp_grad_reduce(MlpTrain t) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= NPAR) return;
-    float s = 0.f;
-    for (int sl = 0; sl < WG_SLICES; ++sl) s += t.gpart[(size_t)sl * NPAR + i];
-    t.grad[i] = s;
-}
-
-// Loss = sum of per-row partials / (B * 26), summed in row order.
-__global__ void __launch_bounds__(64) mlp_loss_reduce(MlpTrain t, int B, float *loss_out) {
-    __shared__ float red[64];
-    float s = 0.f;
-    for (int b = threadIdx.x; b < B; b += 64) s += t.loss_rows[b];
-    red[threadIdx.x] = s;
+    // bias sums and the loss: over the lane groups, then over the waves in order
+    auto over_rows = [](float v) {
+        v += __shfl_xor(v, 16, 64);
+        return v + __shfl_xor(v, 32, 64);
+    };
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        const float s1 = over_rows(db1[nt]), s2 = over_rows(db2[nt]);
+        if (q == 0) {
+            red[w][16 * nt + r] = s1;
+            red[w][64 + 16 * nt + r] = s2;
+        }
+    }
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        const float s3 = over_rows(db3[nt]);
+        if (q == 0 && 16 * nt + r < OUT) red[w][128 + 16 * nt + r] = s3;
+    }
+    for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
+    if (lane == 0) red[w][128 + OUT] = loss;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float tot = 0.f;
-        for (int i = 0; i < 64; ++i) tot += red[i];
-        *loss_out = tot / ((float)B * OUT);
-    }
+    const int i = threadIdx.x;
+    if (i < 128 + OUT + 1)
+        gp[i < 64 ? P_B1 + i : (i < 128 ? P_B2 + i - 64 : (i < 128 + OUT ? P_B3 + i - 128 : NPAR))] =
+            ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
 }
 
-// Adam on the float32 masters, then the bf16 MFMA copies (plain and
-// transposed, zero padded).
-__global__ void __launch_bounds__(256) mlp_adam(MlpTrain t, float lr, float b1, float b2, float eps,
-                                                float c1, float c2) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= NPAR) return;
-    const float g = t.grad[i];
-    const float m = b1 * t.m[i] + (1.f - b1) * g;
-    const float v = b2 * t.v[i] + (1.f - b2) * g * g;
-    t.m[i] = m;
-    t.v[i] = v;
-    t.par[i] = t.par[i] - lr * (m / c1) / (sqrtf(v / c2) + eps);
+// The slices' sums added in order (four threads a quarter of the slices each,
+// then the quarters), into grad, or into an Adam step of the float32 masters;
+// the value after the parameters is the loss, the sum of squares / (B * 26).
+struct Adam {
+    float lr, b1, b2, eps, c1, c2;
+};
+__global__ void __launch_bounds__(256) mlp_reduce(MlpTrain t, int slices, int B, float *grad, Adam ad, float *loss) {
+    __shared__ float part[4][64];
+    const int l = threadIdx.x & 63, s0 = threadIdx.x >> 6, i = blockIdx.x * 64 + l;
+    float s = 0.f;
+    if (i <= NPAR) {
+        float v[WG_SLICES / 4];
+#pragma unroll
+        for (int k = 0; k < WG_SLICES / 4; ++k) {
+            const int sl = WG_SLICES / 4 * s0 + k;
+            v[k] = sl < slices ? t.gpart[(size_t)sl * GP_STRIDE + i] : 0.f;
+        }
+#pragma unroll
+        for (int k = 0; k < WG_SLICES / 4; ++k) s += v[k];
+    }
+    part[s0][l] = s;
+    __syncthreads();
+    if (s0 || i > NPAR) return;
+    const float g = ((part[0][l] + part[1][l]) + part[2][l]) + part[3][l];
+    if (i == NPAR) {
+        if (loss) *loss = g / ((float)B * OUT);
+    } else if (grad) {
+        grad[i] = g;
+    } else {
+        const float m = ad.b1 * t.m[i] + (1.f - ad.b1) * g;
+        const float v = ad.b2 * t.v[i] + (1.f - ad.b2) * g * g;
+        t.m[i] = m;
+        t.v[i] = v;
+        t.par[i] = t.par[i] - ad.lr * (m / ad.c1) / (sqrtf(v / ad.c2) + ad.eps);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -703,23 +767,26 @@ hipError_t hydro_mlp_launch_pack(const MlpTrain &t, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t hydro_mlp_launch_forward(const MlpTrain &t, const float *X, int B, hipStream_t s) {
-    const int waves = (B + 63) / 64;
-    hipLaunchKernelGGL(mlp_train_forward, dim3((waves + 3) / 4), dim3(256), 0, s, t, X, B);
+hipError_t hydro_mlp_launch_forward(const MlpTrain &t, const float *X, int B, float *Y, hipStream_t s) {
+    hipLaunchKernelGGL(mlp_forward, dim3((B + 15) / 16), dim3(64), 0, s, t, X, B, Y);
     return hipGetLastError();
 }
 
-hipError_t hydro_mlp_launch_grad(const MlpTrain &t, const float *T, int B, float *loss, hipStream_t s) {
-    const int waves = (B + 63) / 64;
-    hipLaunchKernelGGL(mlp_train_backward_rows, dim3((waves + 3) / 4), dim3(256), 0, s, t, T, B);
-    hipLaunchKernelGGL(mlp_train_wgrad, dim3(WG_TILES * WG_SLICES), dim3(64), 0, s, t, B);
-    hipLaunchKernelGGL(mlp_grad_reduce, dim3((NPAR + 255) / 256), dim3(256), 0, s, t);
-    if (loss) hipLaunchKernelGGL(mlp_loss_reduce, dim3(1), dim3(64), 0, s, t, B, loss);
+static hipError_t launch_rows(const MlpTrain &t, const float *X, const float *T, int B, float *grad, const Adam &ad,
+                              float *loss, hipStream_t s) {
+    const int groups = (B + 63) / 64, slices = groups < WG_SLICES ? groups : WG_SLICES;
+    hipLaunchKernelGGL(mlp_train_rows, dim3(slices), dim3(256), 0, s, t, X, T, B);
+    hipLaunchKernelGGL(mlp_reduce, dim3((NPAR + 64) / 64), dim3(256), 0, s, t, slices, B, grad, ad, loss);
     return hipGetLastError();
 }
 
-hipError_t hydro_mlp_launch_adam(const MlpTrain &t, float lr, float b1, float b2, float eps, float c1,
-                                 float c2, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_adam, dim3((NPAR + 255) / 256), dim3(256), 0, s, t, lr, b1, b2, eps, c1, c2);
-    return hipGetLastError();
+hipError_t hydro_mlp_launch_grad(const MlpTrain &t, const float *X, const float *T, int B, float *grad, float *loss,
+                                 hipStream_t s) {
+    return launch_rows(t, X, T, B, grad, Adam{}, loss, s);
+}
+
+hipError_t hydro_mlp_launch_step(const MlpTrain &t, const float *X, const float *T, int B, float lr, float b1, float b2,
+                                 float eps, float c1, float c2, float *loss, hipStream_t s) {
+    hipError_t e = launch_rows(t, X, T, B, nullptr, Adam{lr, b1, b2, eps, c1, c2}, loss, s);
+    return e == hipSuccess ? hydro_mlp_launch_pack(t, s) : e;
 }
