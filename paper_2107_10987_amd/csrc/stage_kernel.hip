@@ -1220,49 +1220,102 @@ hipError_t hydro_launch_stage(const StageArgs &a, hipStream_t s) {
 // one-hot id (X [.][34], FP32 of the FP64 values) and the plain PPM values at
 // the 26 points in the same normalisation (T [.][26]); rows are
 // [leaf][cell][field], and valid = 0 marks flat neighbourhoods (sigma = 0).
-__global__ void __launch_bounds__(NT) pairs_kernel(const double *U, const int32_t *gm,
-                                                   const int32_t *prolong, int n_prolong, float *X,
-                                                   float *T, uint8_t *valid) {
-    __shared__ double P[BLOCK_LDS];
-    const int leaf = blockIdx.x;
-    gather_block<NT, true>(P, U, gm, leaf, 0, 3, prolong, n_prolong, threadIdx.x);
+//
+// The output, 241 B a row, is what bounds it.  A workgroup takes one z layer of
+// a leaf, wave f field f and a lane a cell, with the 12 x 12 x 5 box of the
+// layer's stencils in LDS (40 KB: two workgroups per compute unit, and eight
+// times as many as leaves), runs each of the 13 lines once for both its ends,
+// and hands its rows over through 4 KB of LDS of its own, so that they go out
+// as runs of consecutive words (a lane storing its own row touches a line per
+// lane and store) and no wave waits for another.  125 leaves: 109 us with a
+// workgroup per leaf, one point at a time and rows stored by their lanes,
+// 38 us so.
+constexpr int PBX = NX + 4;                       // box edge in x and y
+constexpr int PBN = PBX * PBX * 5;                // box cells
+constexpr int XIN = mlp::IN, TOUT = mlp::OUT;
+
+// Slot in the ghost map of the ghost cell (i, j, k), -3 .. 10: its raster index
+// less the interior cells before it.
+__device__ __forceinline__ int ghost_slot(int i, int j, int k) {
+    auto in = [](int v) { return v >= 0 && v < NX; };
+    auto below = [](int v) { return min(max(v, 0), NX); };
+    const int before = below(k) * NX * NX + (in(k) ? below(j) * NX + (in(j) ? below(i) : 0) : 0);
+    return pidx(i, j, k) - before;
+}
+
+__global__ void __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(4))) pairs_kernel(const double *U, const int32_t *gm,
+                                                        const int32_t *prolong, int n_prolong, float *X,
+                                                        float *T, uint8_t *valid) {
+    __shared__ double box[NF][PBN];
+    __shared__ float rows[NF][32 * XIN];
+    const int leaf = blockIdx.x / NX, layer = blockIdx.x % NX, tid = threadIdx.x;
+    for (int e = tid; e < PBN; e += 64 * NF) {
+        const int i = e % PBX - 2, j = (e / PBX) % PBX - 2, k = e / (PBX * PBX) + layer - 2;
+        double v[NF];
+        if (i >= 0 && i < NX && j >= 0 && j < NX && k >= 0 && k < NX) {
+            const double *q = U + (size_t)leaf * LEAF_STRIDE + (k * NX + j) * NX + i;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[f] = q[f * NC];
+        } else {
+            ghost_values(U, gm[(size_t)leaf * NG + ghost_slot(i, j, k)], 3, prolong, n_prolong, v);
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) box[f][e] = v[f];
+    }
     __syncthreads();
-    for (int e = threadIdx.x; e < NC * NF; e += NT) {
-        const int c = e / NF, f = e - (e / NF) * NF;
-        const int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-        const int pc = pidx(i, j, k);
-        const double *q = P + f * PS;
-        const double qc = q[pc];
-        double sigma = 0.0;
-        for (int o = 0; o < 27; ++o) {
-            const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-            const double d = fabs(q[pc + dx * SX_ + dy * SY_ + dz * SZ_] - qc);
-            sigma = d > sigma ? d : sigma;
+    const int f = tid >> 6, cell = tid & 63;
+    const double *q = box[f] + (2 * PBX + (cell >> 3) + 2) * PBX + (cell & 7) + 2;
+    const double qc = q[0];
+    auto offset = [](int o) { return (o % 3 - 1) + PBX * ((o / 3) % 3 - 1) + PBX * PBX * (o / 9 - 1); };
+    double sigma = 0.0;
+#pragma unroll
+    for (int o = 0; o < 27; ++o) {
+        const double d = fabs(q[offset(o)] - qc);
+        sigma = d > sigma ? d : sigma;
+    }
+    const double rs = sigma > 0.0 ? 1.0 / sigma : 0.0;
+    const size_t row0 = ((size_t)leaf * NC + layer * 64) * NF;   // the layer's rows, cell by cell
+    valid[row0 + cell * NF + f] = sigma > 0.0 ? 1 : 0;
+    // a half of the wave's rows at a time through the wave's own buffer
+    float *buf = rows[f];
+    auto hand_over = [&](float *out, int cols, int h) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
+        float *o = out + (row0 + (size_t)(32 * h) * NF + f) * cols;
+        for (int e = cell; e < 32 * cols; e += 64) o[(size_t)(e / cols) * NF * cols + e % cols] = buf[e];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    for (int h = 0; h < 2; ++h) {
+        if (cell / 32 == h) {
+            float *x = buf + (cell % 32) * XIN;
+#pragma unroll
+            for (int o = 0; o < 27; ++o) x[o] = (float)((q[offset(o)] - qc) * rs);
+#pragma unroll
+            for (int g = 0; g < NF; ++g) x[27 + g] = (g == f) ? 1.f : 0.f;
         }
-        const size_t row = ((size_t)leaf * NC + c) * NF + f;
-        valid[row] = sigma > 0.0 ? 1 : 0;
-        const double rs = sigma > 0.0 ? 1.0 / sigma : 0.0;
-        for (int o = 0; o < 27; ++o) {
-            const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-            X[row * 34 + o] = (float)((q[pc + dx * SX_ + dy * SY_ + dz * SZ_] - qc) * rs);
+        hand_over(X, XIN, h);
+    }
+    float tv[TOUT];
+#pragma unroll
+    for (int l = 0; l < 13; ++l) {
+        const int o = mlp::LINE_DIR[l];   // its first component that is not zero is positive
+        double L, R;
+        ppm_both(q, 0, offset(o), L, R);
+        tv[o < 13 ? o : o - 1] = (float)((R - qc) * rs);
+        tv[26 - o < 13 ? 26 - o : 25 - o] = (float)((L - qc) * rs);
+    }
+    for (int h = 0; h < 2; ++h) {
+        if (cell / 32 == h) {
+#pragma unroll
+            for (int o = 0; o < TOUT; ++o) buf[(cell % 32) * TOUT + o] = tv[o];
         }
-        for (int g = 0; g < NF; ++g) X[row * 34 + 27 + g] = (g == f) ? 1.f : 0.f;
-        for (int o = 0; o < 27; ++o) {
-            if (o == 13) continue;
-            const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-            const bool plus = (dx != 0) ? (dx > 0) : ((dy != 0) ? (dy > 0) : (dz > 0));
-            int st = dx * SX_ + dy * SY_ + dz * SZ_;
-            st = plus ? st : -st;
-            const double v = ppm_end(q, pc, st, plus);
-            T[row * 26 + (o < 13 ? o : o - 1)] = (float)((v - qc) * rs);
-        }
+        hand_over(T, TOUT, h);
     }
 }
 
 hipError_t hydro_launch_pairs(const double *U, const int32_t *gm, const int32_t *prolong, int n_prolong,
                               int n, float *X, float *T, uint8_t *valid, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pairs_kernel, dim3(n), dim3(NT), 0, s, U, gm, prolong, n_prolong, X, T, valid);
+    hipLaunchKernelGGL(pairs_kernel, dim3(n * NX), dim3(64 * NF), 0, s, U, gm, prolong, n_prolong, X, T, valid);
     return hipGetLastError();
 }
 
