@@ -58,8 +58,8 @@ struct hydro_t {
     int64_t mlp_cells = 0;
     int64_t graph_mlp_cells = 0;   // cells the captured graph reconstructs per replay
     std::vector<void *> mlp_bufs;  // everything allocated for the network
-    double *amax = nullptr;    // per-block signal speeds [max_leaves << ts]
-    Status *status = nullptr;  // device status word
+    Status *status = nullptr;  // device status word, and behind it, for one copy to the host,
+    double *amax = nullptr;    // the per-block signal speeds [max_leaves << ts]
     hipStream_t last_stream = nullptr;
     std::string err;
     // stage-kernel timing
@@ -375,13 +375,10 @@ int run_stage(hydro_t *h, const hydro_grid *g, int stage, double dt, const doubl
     return HYDRO_OK;
 }
 
-int read_status(hydro_t *h, hipStream_t s) {
-    Status st;
-    hipError_t e = hipMemcpyAsync(&st, h->status, sizeof(Status), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(h, e, "status read");
+// Report a non-physical result read from the device, and clear the word.
+int check_status(hydro_t *h, const Status &st, hipStream_t s) {
     if (st.flag) {
-        e = hipMemsetAsync(h->status, 0, sizeof(Status), s);
+        hipError_t e = hipMemsetAsync(h->status, 0, sizeof(Status), s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_fail(h, e, "status reset");
         static const char *names[NF] = {"rho", "sx", "sy", "sz", "egas", "tau", "spc"};
@@ -391,6 +388,14 @@ int read_status(hydro_t *h, hipStream_t s) {
         return fail(h, HYDRO_ENONPHYS, buf);
     }
     return HYDRO_OK;
+}
+
+int read_status(hydro_t *h, hipStream_t s) {
+    Status st;
+    hipError_t e = hipMemcpyAsync(&st, h->status, sizeof(Status), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(h, e, "status read");
+    return check_status(h, st, s);
 }
 
 // Autotune table as JSON: {"arch": "...", "schedule": [b0, ..., b15]}.
@@ -685,7 +690,6 @@ int hydro_create(const hydro_params *p, hydro_t **out) {
     e = hipMalloc((void **)&h->U1, n * LEAF_STRIDE * sizeof(double));
     if (e == hipSuccess && h->rk == 3) e = hipMalloc((void **)&h->U2, n * LEAF_STRIDE * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void **)&h->dscr, n * 3 * LEAF_STRIDE * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc((void **)&h->amax, n * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void **)&h->queue, QUEUE_INTS * (1 + NSIDE) * sizeof(int));
     for (int i = 0; i < NSIDE && e == hipSuccess; ++i) {
         e = hipStreamCreateWithFlags(&h->side[i], hipStreamNonBlocking);
@@ -698,9 +702,11 @@ int hydro_create(const hydro_params *p, hydro_t **out) {
     if (e == hipSuccess) e = alloc_mlp(h, n);
     if (e == hipSuccess) e = hipMemset(h->queue, 0, QUEUE_INTS * (1 + NSIDE) * sizeof(int));
     if (e == hipSuccess) e = hipMemset(h->leaf_done, 0, n * sizeof(int));
-    if (e == hipSuccess) e = hipMalloc((void **)&h->status, sizeof(Status));
-    if (e == hipSuccess) e = hipMemset(h->status, 0, sizeof(Status));
-    if (e == hipSuccess) e = hipMemset(h->amax, 0, n * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc((void **)&h->status, sizeof(Status) + n * sizeof(double));
+    if (e == hipSuccess) {
+        h->amax = (double *)(h->status + 1);
+        e = hipMemset(h->status, 0, sizeof(Status) + n * sizeof(double));
+    }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         rc = (e == hipErrorOutOfMemory) ? fail(h, HYDRO_ENOMEM, "workspace allocation")
@@ -724,7 +730,6 @@ int hydro_destroy(hydro_t *h) {
     if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
     if (h->U1) (void)hipFree(h->U1);
     if (h->U2) (void)hipFree(h->U2);
-    if (h->amax) (void)hipFree(h->amax);
     if (h->dscr) (void)hipFree(h->dscr);
     if (h->queue) (void)hipFree(h->queue);
     if (h->leaf_done) (void)hipFree(h->leaf_done);
@@ -748,16 +753,20 @@ int hydro_step(hydro_t *h, const hydro_grid *g, double dt, double *amax_out) {
     if (amax_out) {
         hipStream_t s = (hipStream_t)g->stream;
         const size_t nb = (size_t)g->n << h->ts;
-        std::vector<double> blk(nb);
-        hipError_t e = hipMemcpyAsync(blk.data(), h->amax, sizeof(double) * nb, hipMemcpyDeviceToHost, s);
+        // the status word and the speeds in one copy: each is a round trip
+        std::vector<double> host(sizeof(Status) / sizeof(double) + nb);
+        hipError_t e = hipMemcpyAsync(host.data(), h->status, sizeof(double) * host.size(), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_fail(h, e, "amax copy");
+        Status st;
+        memcpy(&st, host.data(), sizeof st);
+        const double *blk = host.data() + sizeof(Status) / sizeof(double);
         for (int l = 0; l < g->n; ++l) {
             double m = blk[(size_t)l << h->ts];
             for (int t = 1; t < (1 << h->ts); ++t) m = std::max(m, blk[((size_t)l << h->ts) + t]);
             amax_out[l] = m;
         }
-        return read_status(h, s);
+        return check_status(h, st, s);
     }
     return HYDRO_OK;
 }
