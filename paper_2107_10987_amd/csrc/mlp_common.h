@@ -64,28 +64,34 @@ constexpr LineOfDir make_line_of_dir() {
 // toward zero where it came out larger in magnitude (sign-magnitude bits:
 // one less in the integer view is one unit smaller in magnitude).
 __device__ __forceinline__ float rz32(double x) {
-    float f = (float)x;
-    if (fabs((double)f) > fabs(x)) f = __int_as_float(__float_as_int(f) - 1);
-    return f;
+    const float f = (float)x;
+    return __int_as_float(__float_as_int(f) - (fabs((double)f) > fabs(x) ? 1 : 0));
 }
 
-// The plain limiter on a predicted pair of one line (R at +d, L at -d), the
-// cell value qc and its neighbours nbR (at +d) and nbL (at -d): each value
-// clamped between the cell and its neighbour in that direction, then the PPM
-// monotonicity constraint on the pair (unfused FP64).  The results are kept
-// as binary32 offsets from qc (the point value is qc + offset in FP64),
-// rounded toward zero, i.e. toward the cell value, so a clamped end stays
-// between the cell and its neighbour; an end the constraint pulls in
+// fmin and fmax of operands that hold no signalling NaN, which fmin and fmax
+// would first quiet, an instruction each.
+__device__ __forceinline__ double min_of(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double max_of(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// The PPM monotonicity constraint (unfused FP64) of the plain limiter on a
+// predicted pair of one line (r at +d, l at -d), each value already clamped
+// between the cell value qc and its neighbour in that direction.  The results
+// are kept as binary32 offsets from qc (the point value is qc + offset in
+// FP64), rounded toward zero, i.e. toward the cell value, so a clamped end
+// stays between the cell and its neighbour; an end the constraint pulls in
 // (3 qc - 2 R, offset -2 (R - qc)) takes -2 times the other end's rounded
-// offset (exact), so the pair stays on the constraint's boundary.  min/max
-// clamps carry a NaN prediction to a bound; the pre-pass's check fails it.
-__device__ __forceinline__ void learned_limit(double qc, double nbR, double nbL, double R, double L, float &oR,
-                                              float &oL) {
-    const double loR = fmin(qc, nbR), hiR = fmax(qc, nbR);
-    const double loL = fmin(qc, nbL), hiL = fmax(qc, nbL);
-    const double r = fmin(fmax(R, loR), hiR), l = fmin(fmax(L, loL), hiL);
+// offset (exact), so the pair stays on the constraint's boundary.
+__device__ __forceinline__ void learned_limit(double qc, double r, double l, float &oR, float &oL) {
     const bool ext = (r - qc) * (qc - l) <= 0.0;
-    const double D = r - l, M6 = 6.0 * (qc - 0.5 * (l + r));
+    const double D = r - l, M6 = 6.0 * __builtin_fma(-0.5, l + r, qc);
     const double DM = D * M6, DD = D * D;
     const bool lowL = DM > DD, lowR = !lowL & (DM < -DD);
     const float fr = rz32(r - qc), fl = rz32(l - qc);
