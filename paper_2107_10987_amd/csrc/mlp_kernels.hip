@@ -507,7 +507,7 @@ __device__ __forceinline__ bool limit_check_line(double qc, double nbR, double n
     {
         const double D = r - l, M6 = 6.0 * __builtin_fma(-0.5, l + r, qc), DM = D * M6;
         const double lim = __builtin_fma(1e-13 * fabs(D), fabs(l) + fabs(qc) + fabs(r), D * D);
-        const bool mono = ((r - qc) * (qc - l) > 0.0) & !(DM > lim) & !(DM < -lim);
+        const bool mono = ((r - qc) * (qc - l) > 0.0) & !(fabs(DM) > lim);
         ok = ok & (((l == qc) & (r == qc)) | mono);
     }
     return ok;
