@@ -26,12 +26,12 @@ namespace {
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// Forward and training kernels: a wave holds 16 rows.  LDS staging of a wave's
-// bf16 rows of 64, padded to a 68-element (136 B) stride: rows written by
-// columns then fall in different banks, and the 8-byte MFMA operand loads stay
-// aligned.
+// Forward and training kernels: four waves hold 16 rows, wave c the columns
+// 16 c .. 16 c + 15 of every layer.  LDS staging of the bf16 rows of 64, padded
+// to a 68-element (136 B) stride: rows written by columns then fall in
+// different banks, and the 8-byte MFMA operand loads stay aligned.
 constexpr int LDA = 68;
-constexpr int STAGE_ELEMS = 16 * LDA;   // bf16 elements per wave
+constexpr int STAGE_ELEMS = 16 * LDA;   // bf16 elements of 16 rows
 
 __device__ __forceinline__ v4f mfma(v4s a, v4s b, v4f c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -54,28 +54,6 @@ __device__ __forceinline__ float gelu_grad(float z, float t) {
     return 0.5f * (1.0f + t) + 0.5f * z * (1.0f - t * t) * GELU_C * (1.0f + 3.0f * GELU_A * z * z);
 }
 
-// One layer for a wave's 16 rows: Z[r][n] = sum_k A[r][k] W[n][k], A in LDS
-// (bf16, row stride LDA), W bf16 [NTILE * 16][64] in global memory, k below
-// 16 KB (the rest of A is zero).  Results in D layout: z[nt] holds rows 4q + i,
-// column 16 nt + l % 16.
-template <int NTILE, int KB>
-__device__ __forceinline__ void layer(const uint16_t *A, const uint16_t *W, int lane, v4f z[NTILE]) {
-    const int r = lane & 15, q = lane >> 4;
-    v4s b[KB][NTILE];
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int nt = 0; nt < NTILE; ++nt) b[kb][nt] = *(const v4s *)(W + (16 * nt + r) * 64 + 16 * kb + 4 * q);
-#pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt) z[nt] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-        const v4s a = *(const v4s *)(A + r * LDA + 16 * kb + 4 * q);
-#pragma unroll
-        for (int nt = 0; nt < NTILE; ++nt) z[nt] = mfma(a, b[kb][nt], z[nt]);
-    }
-}
-
 // Four values of D-layout rows 4q .. 4q + 3 as bfloat16: rows of one column,
 // which is also how an MFMA operand holds them when the rows are contracted.
 __device__ __forceinline__ v4s pack4(const float v[4]) {
@@ -85,77 +63,99 @@ __device__ __forceinline__ v4s pack4(const float v[4]) {
     return r;
 }
 
-// Column 16 nt + l % 16 of the wave's rows into the staging buffer.
-__device__ __forceinline__ void stage_col(uint16_t *S, int nt, int lane, v4s v) {
-    const int c = lane & 15, q = lane >> 4;
+// A wave's operands of one layer's weights W bf16 [..][64], columns 16 c ..,
+// k below 16 KB.
+template <int KB>
+__device__ __forceinline__ void weights(const uint16_t *W, int c, int lane, v4s b[KB]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) S[(4 * q + i) * LDA + 16 * nt + c] = (uint16_t)v[i];
+    for (int kb = 0; kb < KB; ++kb) b[kb] = *(const v4s *)(W + (16 * c + (lane & 15)) * 64 + 16 * kb + 4 * (lane >> 4));
 }
 
-// The staging buffer is private to its wave, whose LDS accesses are performed
-// in order: only the compiler has to keep them so.
-__device__ __forceinline__ void stage_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
-// Forward pass of the 16 rows row0 .. of X [B][34] (float32; rows past nrows are
-// zero): z and tanh of the two hidden layers (D layout), their bf16
-// activations, and the output layer's columns in y (D layout, bias added).
-struct Forward {
-    v4f z1[4], z2[4], y[2];
-    float t1[4][4], t2[4][4];
-    v4s a1[4], a2[4];
-};
-__device__ __forceinline__ void forward16(const float *X, int row0, int nrows, const uint16_t *Wb, const float *par,
-                                          uint16_t *S, int lane, Forward &o) {
-    const int r = lane & 15, q = lane >> 4;
-    // this lane's operand of the first layer: row r, inputs 16 kb + 4q + i
+// Z[r][n] = sum_k A[r][k] W[n][k] for 16 rows and the wave's 16 columns, A in
+// LDS (bf16, row stride LDA).  D layout: z holds rows 4q + i, column l % 16.
+template <int KB>
+__device__ __forceinline__ v4f layer(const uint16_t *A, const v4s b[KB], int lane) {
+    v4f z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kb = 0; kb < 3; ++kb) {
+    for (int kb = 0; kb < KB; ++kb)
+        z = mfma(*(const v4s *)(A + (lane & 15) * LDA + 16 * kb + 4 * (lane >> 4)), b[kb], z);
+    return z;
+}
+
+// The wave's columns 16 c .. of the rows into the staging buffer.
+__device__ __forceinline__ void stage_col(uint16_t *S, int c, int lane, v4s v) {
+    const int r = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) S[(4 * q + i) * LDA + 16 * c + r] = (uint16_t)v[i];
+}
+
+// The forward pass's weights and biases of a wave's columns: loaded before the
+// first layer, so a call waits for them once.
+struct Net {
+    v4s w1[3], w2[4], w3[4];
+    float b1, b2, b3;
+    __device__ __forceinline__ Net(const MlpTrain &t, int c, int lane) {
+        const int n = 16 * c + (lane & 15);
+        weights<3>(t.wb + WB_W1, c, lane, w1);
+        weights<4>(t.wb + WB_W2, c, lane, w2);
+        if (c < 2) weights<4>(t.wb + WB_W3, c, lane, w3);
+        b1 = t.par[P_B1 + n];
+        b2 = t.par[P_B2 + n];
+        b3 = n < OUT ? t.par[P_B3 + n] : 0.f;
+    }
+};
+
+// Forward pass of the 16 rows row0 .. of X [B][34] (float32; rows past nrows
+// are zero): z and tanh of the two hidden layers, their bf16 activations, and
+// in the waves of columns 0 .. 31 the output layer in y (bias added).  S0 and
+// S1 are the rows' staging buffers; a barrier before each layer.  xcol: where
+// the inputs' columns go as operands of the rows' contraction, or null.
+struct Forward {
+    v4f z1, z2, y;
+    float t1[4], t2[4];
+    v4s a1, a2;
+};
+__device__ __forceinline__ void activate(v4f &z, float b, float t[4], v4s &a, uint16_t *S, int c, int lane) {
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        z[i] += b;
+        t[i] = gelu_tanh(z[i]);
+        v[i] = gelu(z[i], t[i]);
+    }
+    a = pack4(v);
+    stage_col(S, c, lane, a);
+}
+__device__ __forceinline__ void forward16(const float *X, int row0, int nrows, const Net &net, uint16_t *S0,
+                                          uint16_t *S1, int c, int lane, Forward &o, v4s *xcol = nullptr) {
+    const int r = lane & 15, q = lane >> 4;
+    if (c < 3) {   // the first layer's inputs 16 c + 4q + i of row r
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int k = 16 * kb + 4 * q + i;
+            const int k = 16 * c + 4 * q + i;
             v[i] = (r < nrows && k < IN) ? X[(size_t)(row0 + r) * IN + k] : 0.f;
         }
-        *(v4s *)(S + r * LDA + 16 * kb + 4 * q) = pack4(v);
+        *(v4s *)(S0 + r * LDA + 16 * c + 4 * q) = pack4(v);
     }
-    stage_fence();
-    layer<4, 3>(S, Wb + WB_W1, lane, o.z1);
-    stage_fence();
+    __syncthreads();
+    if (xcol && c < 3) {
+        v4s v;
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        float a[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o.z1[nt][i] += par[P_B1 + 16 * nt + r];
-            o.t1[nt][i] = gelu_tanh(o.z1[nt][i]);
-            a[i] = gelu(o.z1[nt][i], o.t1[nt][i]);
-        }
-        o.a1[nt] = pack4(a);
-        stage_col(S, nt, lane, o.a1[nt]);
+        for (int i = 0; i < 4; ++i) v[i] = (short)S0[(4 * q + i) * LDA + 16 * c + r];
+        xcol[c * 4 * 64] = v;
     }
-    stage_fence();
-    layer<4, 4>(S, Wb + WB_W2, lane, o.z2);
-    stage_fence();
+    o.z1 = layer<3>(S0, net.w1, lane);
+    activate(o.z1, net.b1, o.t1, o.a1, S1, c, lane);
+    __syncthreads();
+    o.z2 = layer<4>(S1, net.w2, lane);
+    activate(o.z2, net.b2, o.t2, o.a2, S0, c, lane);
+    __syncthreads();
+    if (c < 2) {
+        o.y = layer<4>(S0, net.w3, lane);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        float a[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o.z2[nt][i] += par[P_B2 + 16 * nt + r];
-            o.t2[nt][i] = gelu_tanh(o.z2[nt][i]);
-            a[i] = gelu(o.z2[nt][i], o.t2[nt][i]);
-        }
-        o.a2[nt] = pack4(a);
-        stage_col(S, nt, lane, o.a2[nt]);
+        for (int i = 0; i < 4; ++i) o.y[i] += net.b3;
     }
-    stage_fence();
-    layer<2, 4>(S, Wb + WB_W3, lane, o.y);
-    stage_fence();
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (16 * nt + r < OUT) o.y[nt][i] += par[P_B3 + 16 * nt + r];
 }
 
 // GELU for inference: 0.5 z (1 + tanh u) = z / (1 + exp(-2u)),
@@ -173,122 +173,118 @@ __device__ __forceinline__ float gelu_fast(float z) {
 // Training
 // ---------------------------------------------------------------------------
 
-// Network outputs Y [B][26] of B rows of X [B][34], one wave per 16 rows: the
-// weights come from L2 into registers and nothing is kept, so a call is one
-// launch of as many waves as the batch has (64 rows per wave left a batch of
-// 1003 on 4 compute units, 60 us; now 8 us).
-__global__ void __launch_bounds__(64) mlp_forward(MlpTrain t, const float *X, int B, float *Y) {
-    __shared__ __attribute__((aligned(16))) uint16_t S[STAGE_ELEMS];
-    const int lane = threadIdx.x, r = lane & 15, q = lane >> 4;
+// Network outputs Y [B][26] of B rows of X [B][34], a workgroup per 16 rows.
+// Bound by the latency of its chain of layers, most of it the 32 tanh a row's
+// lanes have in turn where one wave holds the rows: four waves have eight each
+// (a call on 1003 rows: 7.9 us with one, 6.1 with four).
+__global__ void __launch_bounds__(256) mlp_forward(MlpTrain t, const float *X, int B, float *Y) {
+    __shared__ __attribute__((aligned(16))) uint16_t S[2][STAGE_ELEMS];
+    const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
     const int row0 = blockIdx.x * 16;
+    const Net net(t, c, lane);
     Forward o;
-    forward16(X, row0, B - row0, t.wb, t.par, S, lane, o);
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    forward16(X, row0, B - row0, net, S[0], S[1], c, lane, o);
+    if (c < 2)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int row = row0 + 4 * q + i, col = 16 * nt + r;
-            if (row < B && col < OUT) Y[(size_t)row * OUT + col] = o.y[nt][i];
+            const int row = row0 + 4 * q + i, col = 16 * c + r;
+            if (row < B && col < OUT) Y[(size_t)row * OUT + col] = o.y[i];
         }
 }
 
-// Forward, backward and the partial weight gradients of groups of 64 rows, a
-// wave per 16 rows, in one pass: dY = 2 (y - T) / (B * 26);
+// Forward, backward and the partial weight gradients of groups of 64 rows in
+// one pass, four waves per 16 rows: dY = 2 (y - T) / (B * 26);
 // dZ2 = (dY W3) * gelu'(z2); dZ1 = (dZ2 W2) * gelu'(z1).  Everything stays in
 // registers and LDS.  An MFMA result holds, per lane, four rows of a column,
 // which is an operand of the products dZ^T A over the rows: the waves lay
-// those operands down in LDS (44 KB) and each takes nine of the 36 gradient
-// tiles over the group's rows, and over the groups group, group + grid, ...;
-// the workgroup's sums go to its slice of gpart, where mlp_reduce adds the
-// slices in order (deterministic).  A batch of 4096 is 64 workgroups; its
-// 62 + 73 + 80 us in three kernels with the rows in memory between them take 20.
+// those operands down in LDS (43 KB) and share the 36 gradient tiles over the
+// group's rows, and over the groups group, group + grid, ...; the workgroup's
+// sums go to its slice of gpart, where mlp_reduce adds the slices in order
+// (deterministic).  A batch of 4096 is 64 workgroups, bound by the latency of
+// one group: with a wave per 16 rows, whose lanes have 32 tanh in turn and
+// whose weights are loaded layer by layer, 20 us; so 15.
 constexpr int OP_DY = 0, OP_DZ2 = 2, OP_DZ1 = 6, OP_A2 = 10, OP_A1 = 14, OP_X = 18, OPS = 21;
+constexpr int TRAIN_WAVES = 16, WAVE_TILES = (WG_TILES + TRAIN_WAVES - 1) / TRAIN_WAVES;
 
-__global__ void __launch_bounds__(256) mlp_train_rows(MlpTrain t, const float *X, const float *T, int B) {
-    __shared__ __attribute__((aligned(16))) uint16_t stage[4][STAGE_ELEMS];
+__global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, const float *X, const float *T, int B) {
+    __shared__ __attribute__((aligned(16))) uint16_t stage[4][2][STAGE_ELEMS];
     __shared__ v4s op[OPS][4][64];
     __shared__ float red[4][160];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
-    uint16_t *S = stage[w];
+    int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = wave >> 2, c = wave & 3;   // 16 rows of the group, 16 of their columns
+    uint16_t *S0 = stage[w][0], *S1 = stage[w][1];
     const float scale = 2.0f / ((float)B * OUT);
-    v4f acc[WG_TILES / 4];
+    const Net net(t, c, lane);
+    v4s w3t[2], w2t[4];
+    weights<2>(t.wbT + WB_W3T, c, lane, w3t);
+    weights<4>(t.wbT + WB_W2T, c, lane, w2t);
+    v4f acc[WAVE_TILES];
 #pragma unroll
-    for (int j = 0; j < WG_TILES / 4; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
-    float db1[4] = {0.f, 0.f, 0.f, 0.f}, db2[4] = {0.f, 0.f, 0.f, 0.f}, db3[2] = {0.f, 0.f}, loss = 0.f;
+    for (int j = 0; j < WAVE_TILES; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    float db1 = 0.f, db2 = 0.f, db3 = 0.f, loss = 0.f;
     for (int g = blockIdx.x; 64 * g < B; g += gridDim.x) {
-        const int row0 = 64 * g + 16 * w, nrows = min(16, B - row0);   // nrows <= 0: an empty wave
-        const v4s zero = {0, 0, 0, 0};
-        Forward o;
-        forward16(X, row0, nrows, t.wb, t.par, S, lane, o);
-        // dY, its bias sums and the loss (columns 26..31 are zero)
+        const int row0 = 64 * g + 16 * w, nrows = min(16, B - row0);   // nrows <= 0: no rows left
+        asm volatile("" : "+v"(lane));   // addresses are formed here, not kept from before the loop
+        const int r = lane & 15, q = lane >> 4;
+        float tgt[4];
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int i = 0; i < 4; ++i) {
+            const int row = 4 * q + i, col = 16 * c + r;
+            tgt[i] = row < nrows && col < OUT ? T[(size_t)(row0 + row) * OUT + col] : 0.f;
+        }
+        Forward o;
+        forward16(X, row0, nrows, net, S0, S1, c, lane, o, &op[OP_X][w][lane]);
+        if (c < 2) {   // dY, its bias sums and the loss (columns 26..31 are zero)
             float d[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int row = 4 * q + i, col = 16 * nt + r;
                 d[i] = 0.f;
-                if (row < nrows && col < OUT) {
-                    const float e = o.y[nt][i] - T[(size_t)(row0 + row) * OUT + col];
+                if (4 * q + i < nrows && 16 * c + r < OUT) {
+                    const float e = o.y[i] - tgt[i];
                     loss += e * e;
                     d[i] = scale * e;
                 }
-                db3[nt] += d[i];
+                db3 += d[i];
             }
             const v4s v = pack4(d);
-            stage_col(S, nt, lane, v);
-            op[OP_DY + nt][w][lane] = v;
+            stage_col(S1, c, lane, v);
+            op[OP_DY + c][w][lane] = v;
         }
-        stage_fence();
-        // dA2[r][h] = sum_o dY[r][o] W3[o][h]
-        v4f z[4];
-        layer<4, 2>(S, t.wbT + WB_W3T, lane, z);
-        stage_fence();
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        __syncthreads();
+        {   // dA2[r][h] = sum_o dY[r][o] W3[o][h]
+            const v4f z = layer<2>(S1, w3t, lane);
             float d[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                d[i] = 4 * q + i < nrows ? z[nt][i] * gelu_grad(o.z2[nt][i], o.t2[nt][i]) : 0.f;
-                db2[nt] += d[i];
+                d[i] = 4 * q + i < nrows ? z[i] * gelu_grad(o.z2[i], o.t2[i]) : 0.f;
+                db2 += d[i];
             }
             const v4s v = pack4(d);
-            stage_col(S, nt, lane, v);
-            op[OP_DZ2 + nt][w][lane] = v;
+            stage_col(S0, c, lane, v);
+            op[OP_DZ2 + c][w][lane] = v;
         }
-        stage_fence();
-        layer<4, 4>(S, t.wbT + WB_W2T, lane, z);
-        stage_fence();
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        __syncthreads();
+        {
+            const v4f z = layer<4>(S0, w2t, lane);
             float d[4];
-            v4s a1 = o.a1[nt], a2 = o.a2[nt];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const bool in = 4 * q + i < nrows;
-                d[i] = in ? z[nt][i] * gelu_grad(o.z1[nt][i], o.t1[nt][i]) : 0.f;
-                db1[nt] += d[i];
-                if (!in) a1[i] = a2[i] = 0;
+                d[i] = in ? z[i] * gelu_grad(o.z1[i], o.t1[i]) : 0.f;
+                db1 += d[i];
+                if (!in) o.a1[i] = o.a2[i] = 0;
             }
-            op[OP_DZ1 + nt][w][lane] = pack4(d);
-            op[OP_A1 + nt][w][lane] = a1;
-            op[OP_A2 + nt][w][lane] = a2;
-        }
-#pragma unroll
-        for (int nt = 0; nt < 3; ++nt) {
-            float v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = 4 * q + i, k = 16 * nt + r;
-                v[i] = (row < nrows && k < IN) ? X[(size_t)(row0 + row) * IN + k] : 0.f;
-            }
-            op[OP_X + nt][w][lane] = nrows > 0 ? pack4(v) : zero;
+            op[OP_DZ1 + c][w][lane] = pack4(d);
+            op[OP_A1 + c][w][lane] = o.a1;
+            op[OP_A2 + c][w][lane] = o.a2;
         }
         __syncthreads();
-        // tiles w, w + 4, ...: 0..7 W3 (2 x 4), 8..23 W2 (4 x 4), 24..35 W1 (4 x 3)
+        // tiles wave, wave + 16, ...: 0..7 W3 (2 x 4), 8..23 W2 (4 x 4), 24..35 W1 (4 x 3)
 #pragma unroll
-        for (int j = 0; j < WG_TILES / 4; ++j) {
-            const int tile = 4 * j + w;
+        for (int j = 0; j < WAVE_TILES; ++j) {
+            const int tile = TRAIN_WAVES * j + wave;
+            if (tile >= WG_TILES) break;
             const int oa = tile < 8 ? OP_DY + tile / 4 : (tile < 24 ? OP_DZ2 + (tile - 8) / 4 : OP_DZ1 + (tile - 24) / 3);
             const int ob = tile < 8 ? OP_A2 + tile % 4 : (tile < 24 ? OP_A1 + tile % 4 : OP_X + (tile - 24) % 3);
 #pragma unroll
@@ -297,9 +293,11 @@ __global__ void __launch_bounds__(256) mlp_train_rows(MlpTrain t, const float *X
         __syncthreads();   // the operands are replaced by the next group's
     }
     float *gp = t.gpart + (size_t)blockIdx.x * GP_STRIDE;
+    const int r = lane & 15, q = lane >> 4;
 #pragma unroll
-    for (int j = 0; j < WG_TILES / 4; ++j) {
-        const int tile = 4 * j + w;
+    for (int j = 0; j < WAVE_TILES; ++j) {
+        const int tile = TRAIN_WAVES * j + wave;
+        if (tile >= WG_TILES) break;
         const int mt = tile < 8 ? tile / 4 : (tile < 24 ? (tile - 8) / 4 : (tile - 24) / 3);
         const int nt = tile < 24 ? tile % 4 : (tile - 24) % 3;
         const int ofs = tile < 8 ? P_W3 : (tile < 24 ? P_W2 : P_W1);
@@ -310,31 +308,27 @@ __global__ void __launch_bounds__(256) mlp_train_rows(MlpTrain t, const float *X
             if (m < rows && n < cols) gp[ofs + m * cols + n] = acc[j][i];
         }
     }
-    // bias sums and the loss: over the lane groups, then over the waves in order
+    // bias sums and the loss (two waves' columns): over the lane groups, then
+    // over the rows' waves in order
     auto over_rows = [](float v) {
         v += __shfl_xor(v, 16, 64);
         return v + __shfl_xor(v, 32, 64);
     };
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const float s1 = over_rows(db1[nt]), s2 = over_rows(db2[nt]);
-        if (q == 0) {
-            red[w][16 * nt + r] = s1;
-            red[w][64 + 16 * nt + r] = s2;
-        }
-    }
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-        const float s3 = over_rows(db3[nt]);
-        if (q == 0 && 16 * nt + r < OUT) red[w][128 + 16 * nt + r] = s3;
+    const float s1 = over_rows(db1), s2 = over_rows(db2), s3 = over_rows(db3);
+    if (q == 0) {
+        red[w][16 * c + r] = s1;
+        red[w][64 + 16 * c + r] = s2;
+        if (16 * c + r < OUT) red[w][128 + 16 * c + r] = s3;
     }
     for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
-    if (lane == 0) red[w][128 + OUT] = loss;
+    if (lane == 0 && c < 2) red[w][128 + OUT + c] = loss;
     __syncthreads();
     const int i = threadIdx.x;
-    if (i < 128 + OUT + 1)
-        gp[i < 64 ? P_B1 + i : (i < 128 ? P_B2 + i - 64 : (i < 128 + OUT ? P_B3 + i - 128 : NPAR))] =
-            ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
+    if (i < 128 + OUT + 1) {
+        float v = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
+        if (i == 128 + OUT) v += ((red[0][i + 1] + red[1][i + 1]) + red[2][i + 1]) + red[3][i + 1];
+        gp[i < 64 ? P_B1 + i : (i < 128 ? P_B2 + i - 64 : (i < 128 + OUT ? P_B3 + i - 128 : NPAR))] = v;
+    }
 }
 
 // The slices' sums added in order (four threads a quarter of the slices each,
@@ -790,14 +784,14 @@ hipError_t hydro_mlp_launch_pack(const MlpTrain &t, hipStream_t s) {
 }
 
 hipError_t hydro_mlp_launch_forward(const MlpTrain &t, const float *X, int B, float *Y, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_forward, dim3((B + 15) / 16), dim3(64), 0, s, t, X, B, Y);
+    hipLaunchKernelGGL(mlp_forward, dim3((B + 15) / 16), dim3(256), 0, s, t, X, B, Y);
     return hipGetLastError();
 }
 
 static hipError_t launch_rows(const MlpTrain &t, const float *X, const float *T, int B, float *grad, const Adam &ad,
                               float *loss, hipStream_t s) {
     const int groups = (B + 63) / 64, slices = groups < WG_SLICES ? groups : WG_SLICES;
-    hipLaunchKernelGGL(mlp_train_rows, dim3(slices), dim3(256), 0, s, t, X, T, B);
+    hipLaunchKernelGGL(mlp_train_rows, dim3(slices), dim3(64 * TRAIN_WAVES), 0, s, t, X, T, B);
     hipLaunchKernelGGL(mlp_reduce, dim3((NPAR + 64) / 64), dim3(256), 0, s, t, slices, B, grad, ad, loss);
     return hipGetLastError();
 }

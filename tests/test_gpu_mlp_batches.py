@@ -1,6 +1,6 @@
 """The network's forward pass and gradients at the edges of their tiles: 16
-rows a wave, 64 a workgroup, 64 workgroups before a workgroup takes a second
-group of rows.
+rows in four waves, 64 a workgroup, 64 workgroups before a workgroup takes a
+second group of rows.
 
 Tolerances: a row's outputs do not depend on the batch (bit for bit); loss
 and gradients against the bf16-emulating oracle as in test_gpu_mlp.py (1e-4
