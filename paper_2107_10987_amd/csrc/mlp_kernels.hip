@@ -331,43 +331,6 @@ __global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, c
     }
 }
 
-// The slices' sums added in order (four threads a quarter of the slices each,
-// then the quarters), into grad, or into an Adam step of the float32 masters;
-// the value after the parameters is the loss, the sum of squares / (B * 26).
-struct Adam {
-    float lr, b1, b2, eps, c1, c2;
-};
-__global__ void __launch_bounds__(256) mlp_reduce(MlpTrain t, int slices, int B, float *grad, Adam ad, float *loss) {
-    __shared__ float part[4][64];
-    const int l = threadIdx.x & 63, s0 = threadIdx.x >> 6, i = blockIdx.x * 64 + l;
-    float s = 0.f;
-    if (i <= NPAR) {
-        float v[WG_SLICES / 4];
-#pragma unroll
-        for (int k = 0; k < WG_SLICES / 4; ++k) {
-            const int sl = WG_SLICES / 4 * s0 + k;
-            v[k] = sl < slices ? t.gpart[(size_t)sl * GP_STRIDE + i] : 0.f;
-        }
-#pragma unroll
-        for (int k = 0; k < WG_SLICES / 4; ++k) s += v[k];
-    }
-    part[s0][l] = s;
-    __syncthreads();
-    if (s0 || i > NPAR) return;
-    const float g = ((part[0][l] + part[1][l]) + part[2][l]) + part[3][l];
-    if (i == NPAR) {
-        if (loss) *loss = g / ((float)B * OUT);
-    } else if (grad) {
-        grad[i] = g;
-    } else {
-        const float m = ad.b1 * t.m[i] + (1.f - ad.b1) * g;
-        const float v = ad.b2 * t.v[i] + (1.f - ad.b2) * g * g;
-        t.m[i] = m;
-        t.v[i] = v;
-        t.par[i] = t.par[i] - ad.lr * (m / ad.c1) / (sqrtf(v / ad.c2) + ad.eps);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Inference weight image
 // ---------------------------------------------------------------------------
@@ -445,6 +408,107 @@ __global__ void __launch_bounds__(256) mlp_pack(MlpTrain t) {
     if (i < 32) {
         const int o = output_of(i);
         t.bi[BI_B3 + i] = o >= 0 ? t.par[P_B3 + o] : 0.f;
+    }
+}
+
+namespace {
+
+// Hidden unit h's place among the inference image's columns: k block, lane
+// group and element (the inverse of hidden_of).
+struct HiddenPlace {
+    int kb, q, j;
+    __device__ explicit HiddenPlace(int h) : kb(h >> 5), q((h >> 2) & 3), j((h & 3) + ((h >> 4) & 1) * 4) {}
+};
+
+// Output o's line (0..12), + 16 where it is the line's -d end.
+__constant__ LineOfDir c_line_of = make_line_of_dir();
+
+// A new value x of parameter i into the bf16 copies and the image (mlp_pack's
+// entries of i), except the image's first bias.
+__device__ __forceinline__ void repack(const MlpTrain &t, int i, float x) {
+    const uint16_t b = bf16_bits(x);
+    if (i < P_B1) {
+        const int n = i / IN, k = i % IN;
+        t.wb[WB_W1 + n * 64 + k] = b;
+        if (k < NNB) t.wbi[512 * (n >> 4) + 8 * (16 * (k >> 3) + (n & 15)) + (k & 7)] = b;
+    } else if (i < P_W2) {   // the first bias
+    } else if (i < P_B2) {
+        const int n = (i - P_W2) / HID, k = (i - P_W2) % HID;
+        const HiddenPlace h(k);
+        t.wb[WB_W2 + n * 64 + k] = b;
+        t.wbT[WB_W2T + k * 64 + n] = b;
+        t.wbi[512 * (4 + 2 * (n >> 4) + h.kb) + 8 * (16 * h.q + (n & 15)) + h.j] = b;
+    } else if (i < P_W3) {
+        t.bi[BI_B2 + i - P_B2] = x;
+    } else if (i < P_B3) {
+        const int n = (i - P_W3) / HID, k = (i - P_W3) % HID, lt = c_line_of.v[n < 13 ? n : n + 1];
+        const HiddenPlace h(k);
+        t.wb[WB_W3 + n * 64 + k] = b;
+        t.wbT[WB_W3T + k * 64 + n] = b;
+        t.wbi[512 * (12 + 2 * (lt >> 4) + h.kb) + 8 * (16 * h.q + (lt & 15)) + h.j] = b;
+    } else {
+        const int n = i - P_B3;
+        t.bi[BI_B3 + c_line_of.v[n < 13 ? n : n + 1]] = x;
+    }
+}
+
+// Parameter of the reduction's place l: the first 512 places hold, eight to a
+// hidden unit, its seven one-hot weights and its first bias, which the image's
+// first bias adds up; then the other first weights; then the rest in order.
+constexpr int COUPLED = 8 * HID;
+__device__ __forceinline__ int param_of(int l) {
+    if (l < COUPLED) return (l & 7) < NF ? P_W1 + (l >> 3) * IN + NNB + (l & 7) : P_B1 + (l >> 3);
+    if (l < P_W2) return P_W1 + (l - COUPLED) / NNB * IN + (l - COUPLED) % NNB;
+    return l;
+}
+static_assert(COUPLED + HID * NNB == P_W2, "places and parameters");
+
+}  // namespace
+
+// The slices' sums added in order (four threads a quarter of the slices each,
+// then the quarters), into grad, or into an Adam step of the float32 masters
+// and of their bf16 copies (a launch of mlp_pack after it took 4 us of a
+// step's 24); the value after the parameters is the loss, the sum of squares /
+// (B * 26).
+struct Adam {
+    float lr, b1, b2, eps, c1, c2;
+};
+__global__ void __launch_bounds__(256) mlp_reduce(MlpTrain t, int slices, int B, float *grad, Adam ad, float *loss) {
+    __shared__ float part[4][64];
+    const int l = threadIdx.x & 63, s0 = threadIdx.x >> 6, place = blockIdx.x * 64 + l;
+    const int i = place <= NPAR ? param_of(place) : place;
+    float s = 0.f;
+    if (i <= NPAR) {
+        float v[WG_SLICES / 4];
+#pragma unroll
+        for (int k = 0; k < WG_SLICES / 4; ++k) {
+            const int sl = WG_SLICES / 4 * s0 + k;
+            v[k] = sl < slices ? t.gpart[(size_t)sl * GP_STRIDE + i] : 0.f;
+        }
+#pragma unroll
+        for (int k = 0; k < WG_SLICES / 4; ++k) s += v[k];
+    }
+    part[s0][l] = s;
+    __syncthreads();
+    if (s0 || i > NPAR) return;
+    const float g = ((part[0][l] + part[1][l]) + part[2][l]) + part[3][l];
+    if (i == NPAR) {
+        if (loss) *loss = g / ((float)B * OUT);
+    } else if (grad) {
+        grad[i] = g;
+    } else {
+        const float m = ad.b1 * t.m[i] + (1.f - ad.b1) * g;
+        const float v = ad.b2 * t.v[i] + (1.f - ad.b2) * g * g;
+        const float x = t.par[i] - ad.lr * (m / ad.c1) / (sqrtf(v / ad.c2) + ad.eps);
+        t.m[i] = m;
+        t.v[i] = v;
+        t.par[i] = x;
+        repack(t, i, x);
+        if (place < COUPLED) {   // a whole wave: this block is all one-hot weights and first biases
+            const float b1 = __shfl(x, l | 7, 64);
+            const int f = l & 7, u = place >> 3;
+            if (f < NF) t.bi[BI_B1 + HID * f + u] = b1 + bf16_float(bf16_bits(x));
+        }
     }
 }
 
@@ -803,6 +867,5 @@ hipError_t hydro_mlp_launch_grad(const MlpTrain &t, const float *X, const float 
 
 hipError_t hydro_mlp_launch_step(const MlpTrain &t, const float *X, const float *T, int B, float lr, float b1, float b2,
                                  float eps, float c1, float c2, float *loss, hipStream_t s) {
-    hipError_t e = launch_rows(t, X, T, B, nullptr, Adam{lr, b1, b2, eps, c1, c2}, loss, s);
-    return e == hipSuccess ? hydro_mlp_launch_pack(t, s) : e;
+    return launch_rows(t, X, T, B, nullptr, Adam{lr, b1, b2, eps, c1, c2}, loss, s);
 }
