@@ -37,7 +37,7 @@ struct hydro_t {
     hipEvent_t fork_ev = nullptr;
     hipEvent_t join_ev[NSIDE] = {};
     int *leaf_done = nullptr;  // [max_leaves]
-    double *tile_amax = nullptr;  // [max_leaves][MAX_PARTS]
+    double *tile_amax = nullptr;  // [max_leaves][MAX_PARTS][PART_WAVES]
     double *bflux = nullptr;   // flux correction: [max_leaves][6][7][64]
     int num_cu = 0;
     int32_t table[HYDRO_NBUCKET];  // schedule per launch-size bucket (HYDRO_SCHED_AUTO)
@@ -697,7 +697,7 @@ int hydro_create(const hydro_params *p, hydro_t **out) {
     }
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipMalloc((void **)&h->leaf_done, n * sizeof(int));
-    if (e == hipSuccess) e = hipMalloc((void **)&h->tile_amax, n * MAX_PARTS * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc((void **)&h->tile_amax, n * MAX_PARTS * PART_WAVES * sizeof(double));
     if (e == hipSuccess && p->reflux) e = hipMalloc((void **)&h->bflux, n * BFLUX_STRIDE * sizeof(double));
     if (e == hipSuccess) e = alloc_mlp(h, n);
     if (e == hipSuccess) e = hipMemset(h->queue, 0, QUEUE_INTS * (1 + NSIDE) * sizeof(int));

@@ -35,6 +35,7 @@ struct Status {
 };
 
 constexpr int MAX_PARTS = 8;   // workgroups a leaf is split over
+constexpr int PART_WAVES = 12; // waves of each
 
 struct StageArgs {
     const double *Uin;        // [n][7][512] stage input (ghost source)
@@ -64,7 +65,7 @@ struct StageArgs {
     int *queue;               // [QUEUE_INTS]: next item of each XCD's range, workgroups
                               // finished (zero between launches)
     int *leaf_done;           // [n] parts finished per leaf (zero between launches)
-    double *tile_amax;        // [n][MAX_PARTS]
+    double *tile_amax;        // [n][MAX_PARTS][PART_WAVES]
     // learned reconstruction (null: plain PPM)
     const float *mlp_off;     // [n][7][13][896][2] learned point values as binary32 offsets
                               // from the cell value (field, line, slot, +d / -d end)

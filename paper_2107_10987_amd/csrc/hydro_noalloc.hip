@@ -20,13 +20,13 @@ namespace {
 constexpr int MAXL = HYDRO_NOALLOC_MAX_LEAVES;
 // scratch layout, in doubles: the stage-1 state [MAXL][7][512], the column
 // walk's per-axis flux differences [MAXL][3][7][512], per-leaf signal speeds
-// [MAXL] (when the caller passes none), the leaves' parts' maxima
-// [MAXL][MAX_PARTS] and counters [MAXL], and the status word (16 bytes)
+// [MAXL] (when the caller passes none), the leaves' parts' waves' speeds
+// [MAXL][MAX_PARTS][PART_WAVES] and counters [MAXL], and the status word (16 bytes)
 constexpr size_t OFF_U1 = 0;
 constexpr size_t OFF_W = OFF_U1 + (size_t)MAXL * LEAF_STRIDE;
 constexpr size_t OFF_AMAX = OFF_W + (size_t)MAXL * 3 * LEAF_STRIDE;
 constexpr size_t OFF_PART = OFF_AMAX + MAXL;
-constexpr size_t OFF_DONE = OFF_PART + MAXL * MAX_PARTS;
+constexpr size_t OFF_DONE = OFF_PART + MAXL * MAX_PARTS * PART_WAVES;
 constexpr size_t OFF_STATUS = OFF_DONE + MAXL / 2;
 constexpr size_t SCRATCH_DOUBLES = OFF_STATUS + 2;
 static_assert(sizeof(Status) <= 2 * sizeof(double), "status word must fit its slot");
