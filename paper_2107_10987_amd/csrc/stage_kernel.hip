@@ -981,8 +981,8 @@ __device__ __forceinline__ void join_parts(const StageArgs &a, double *P, const 
 // LDS and an equal share of the 32 tasks, at eight one task per SIMD (a task is
 // the walk's unit of latency: more parts gain nothing); a leaf's parts are
 // neighbours in the launch order of one XCD.  Per stage launch, whole leaves
-// against parts: one leaf 61 against 19 us, 64 leaves 65 against 29, 120
-// leaves 68 against 45.
+// against parts: one leaf 61 against 18.5 us, 64 leaves 65 against 30, 120
+// leaves 68 against 46.
 template <bool LEARNED, bool PROLONG>
 __global__ void __launch_bounds__(NTC) stage_kernel_col(StageArgs a) {
     __shared__ double P[BLOCK_LDS + NTC / 64];
