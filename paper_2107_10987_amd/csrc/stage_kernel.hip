@@ -287,6 +287,49 @@ __device__ __forceinline__ double wave_max(double v) {
 
 typedef __attribute__((address_space(3))) double *lds_ptr;
 
+// prolong_values of row r, with the loads of all seven source cells in flight
+// together (of the first cell where a source is a mean, whose others follow);
+// NaN for a row the grid does not have.
+__device__ __forceinline__ void prolong_row(const double *U, const int32_t *prolong, int r, int n_prolong, int lg,
+                                            double v[NF]) {
+    if (!prolong || r >= n_prolong) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f] = __builtin_nan("");
+        return;
+    }
+    constexpr int NS = PROLONG_ROW - 1;
+    const size_t fs = (size_t)1 << (3 * lg);
+    const int E = 1 << lg, E2 = E * E;
+    int src[PROLONG_ROW];
+#pragma unroll
+    for (int k = 0; k < PROLONG_ROW; ++k) src[k] = prolong[(size_t)r * PROLONG_ROW + k];
+    double u[NS][NF];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const double *q = U + src_offset(src[k] >= 0 ? src[k] : -src[k] - 1, lg);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) u[k][f] = q[f * fs];
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+        if (src[k] < 0) {
+            const double *q = U + src_offset(-src[k] - 1, lg);
+#pragma unroll
+            for (int f = 0; f < NF; ++f, q += fs)
+                u[k][f] = (((((((0.0 + u[k][f]) + q[1]) + q[E]) + q[E + 1]) + q[E2]) + q[E2 + 1]) + q[E2 + E] +
+                           q[E2 + E + 1]) * 0.125;
+        }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) v[f] = u[0][f];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double frac = ((src[NS] >> a) & 1) ? 0.25 : -0.25;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            v[f] = v[f] + frac * minmod2(u[2 + 2 * a][f] - u[0][f], u[0][f] - u[1 + 2 * a][f]);
+    }
+}
+
 // Ghost-padded 14^3 block of block b into LDS (NTH threads cooperate): its
 // 8^3 cells from U, its ghost cells through the ghost map (a copy, or the mean
 // of the 2x2x2 cells of a finer leaf, summed in z, y, x order, or a
@@ -296,10 +339,13 @@ typedef __attribute__((address_space(3))) double *lds_ptr;
 // before any LDS store, so that each thread waits on memory about twice
 // rather than once per ghost cell.  Threads past the end of a range load and
 // store the last element again (the same value to the same place).  PROLONG:
-// the grid has prolongation rows (without, a row is NaN); the thirty values an
+// the grid has prolongation rows (without, a row is NaN); the fifty values an
 // entry then has in flight would cost the plain walk's kernel its registers
-// (0.7% of a step of the binary), and one field after the other, each waiting on
-// memory, they cost a 664-leaf star a fifth of its step (1.79 against 1.45 ms).
+// (0.7% of a step of the binary).  The entries that are formed, a few hundred
+// of a leaf's 2232 and spread over all waves, are listed in LDS first, rows
+// from the front and means from the back, so that a thread forms one of them
+// and not up to three in turn beside idle lanes (two steps of a 664-leaf star:
+// 1.44 ms with each formed where it is met, 1.35 so).
 template <int NTH, bool PROLONG>
 __device__ __forceinline__ void gather_block(double *P, const double *U, const int32_t *gm, int b,
                                              int ts, int lg, const int32_t *prolong, int n_prolong,
@@ -309,8 +355,14 @@ __device__ __forceinline__ void gather_block(double *P, const double *U, const i
     constexpr int NI = (LEAF_STRIDE + NTH - 1) / NTH;
     constexpr int NGI = (NG + NTH - 1) / NTH;
     const int32_t *g = gm + (size_t)b * NG;
+    __shared__ uint16_t formed[PROLONG ? NG : 1];
+    __shared__ int nformed[2];
     double v[NI];
     int srcs[NGI], pads[NGI];
+    if (PROLONG) {
+        if (tid < 2) nformed[tid] = 0;
+        __syncthreads();
+    }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const int e = min(tid + i * NTH, LEAF_STRIDE - 1);
@@ -346,16 +398,37 @@ __device__ __forceinline__ void gather_block(double *P, const double *U, const i
         if (src >= 0) {
 #pragma unroll
             for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = gv[i][f];
-        } else if (PROLONG || src < -PROLONG_BASE) {
-            double gs[NF];
-            ghost_values(U, src, lg, PROLONG ? prolong : nullptr, n_prolong, gs);
+        } else if (PROLONG) {
+            continue;
+        } else if (src < -PROLONG_BASE) {
 #pragma unroll
-            for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = gs[f];
+            for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = __builtin_nan("");
         } else {
             const double *q = U + src_offset(-src - 1, lg);
 #pragma unroll
             for (int f = 0; f < NF; ++f) P[f * PS + pads[i]] = mean_value(q + f * fs, lg);
         }
+    }
+    if (!PROLONG) return;
+#pragma unroll
+    for (int i = 0; i < NGI; ++i) {
+        const int sl = tid + i * NTH;
+        const bool row = srcs[i] < -PROLONG_BASE;
+        if (sl < NG && srcs[i] < 0) formed[row ? atomicAdd(&nformed[0], 1) : NG - 1 - atomicAdd(&nformed[1], 1)] = sl;
+    }
+    __syncthreads();
+    for (int e = tid; e < nformed[0]; e += NTH) {
+        const int sl = formed[e], r = -g[sl] - PROLONG_BASE - 1, pad = c_ghost_pad[sl];
+        double u[NF];
+        prolong_row(U, prolong, r, n_prolong, lg, u);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) P[f * PS + pad] = u[f];
+    }
+    for (int e = NTH - 1 - tid; e < nformed[1]; e += NTH) {   // other waves than the rows', where there are
+        const int sl = formed[NG - 1 - e], pad = c_ghost_pad[sl];
+        const double *q = U + src_offset(-g[sl] - 1, lg);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) P[f * PS + pad] = mean_value(q + f * fs, lg);
     }
 }
 
