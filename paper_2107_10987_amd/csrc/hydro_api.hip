@@ -481,12 +481,12 @@ hipError_t mlp_alloc(hydro_t *h, T **p, size_t count) {
 }
 
 // Network parameters, Adam state and training workspace (always: one
-// allocation of at most 2.3 MB), plus the per-leaf inference outputs when the
+// allocation of at most 4.4 MB), plus the per-leaf inference outputs when the
 // learned path is on.
 hipError_t alloc_mlp(hydro_t *h, size_t nleaves) {
     h->mlp_batch = h->p.mlp_batch > 0 ? h->p.mlp_batch : 4096;
     mlp::MlpTrain &t = h->mt;
-    const size_t slices = std::min(((size_t)h->mlp_batch + 63) / 64, (size_t)mlp::WG_SLICES);
+    const size_t slices = std::min(((size_t)h->mlp_batch + mlp::TRAIN_ROWS - 1) / mlp::TRAIN_ROWS, (size_t)mlp::WG_SLICES);
     char *base = nullptr;
     size_t end = 0;
     auto place = [&](auto **p, size_t count) {   // nothing but sizes while base is null

@@ -22,7 +22,7 @@ constexpr int NNB = 27;
 // weight-gradient reduction: 36 MFMA tiles (W3 2 x 4, W2 4 x 4, W1 4 x 3) per
 // slice of the batch; at most WG_SLICES slices of GP_STRIDE sums (the
 // parameters' and the loss)
-constexpr int WG_TILES = 36, WG_SLICES = 64, GP_STRIDE = 8192;
+constexpr int WG_TILES = 36, TRAIN_ROWS = 32, WG_SLICES = 128, GP_STRIDE = 8192;
 constexpr int WBI_SIZE = 8192;
 constexpr int BI_B1 = 0, BI_B2 = 448, BI_B3 = 512, BI_SIZE = 544;
 // cells whose reconstruction a leaf's fluxes need: 512 interior + 6 x 64

@@ -127,7 +127,7 @@ __device__ __forceinline__ void activate(v4f &z, float b, float t[4], v4s &a, ui
     stage_col(S, c, lane, a);
 }
 __device__ __forceinline__ void forward16(const float *X, int row0, int nrows, const Net &net, uint16_t *S0,
-                                          uint16_t *S1, int c, int lane, Forward &o, v4s *xcol = nullptr) {
+                                          uint16_t *S1, int c, int lane, Forward &o, v4s *xcol = nullptr, int xstep = 0) {
     const int r = lane & 15, q = lane >> 4;
     if (c < 3) {   // the first layer's inputs 16 c + 4q + i of row r
         float v[4];
@@ -143,7 +143,7 @@ __device__ __forceinline__ void forward16(const float *X, int row0, int nrows, c
         v4s v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = (short)S0[(4 * q + i) * LDA + 16 * c + r];
-        xcol[c * 4 * 64] = v;
+        xcol[c * xstep] = v;
     }
     o.z1 = layer<3>(S0, net.w1, lane);
     activate(o.z1, net.b1, o.t1, o.a1, S1, c, lane);
@@ -192,24 +192,28 @@ __global__ void __launch_bounds__(256) mlp_forward(MlpTrain t, const float *X, i
         }
 }
 
-// Forward, backward and the partial weight gradients of groups of 64 rows in
+// Forward, backward and the partial weight gradients of groups of 32 rows in
 // one pass, four waves per 16 rows: dY = 2 (y - T) / (B * 26);
 // dZ2 = (dY W3) * gelu'(z2); dZ1 = (dZ2 W2) * gelu'(z1).  Everything stays in
 // registers and LDS.  An MFMA result holds, per lane, four rows of a column,
 // which is an operand of the products dZ^T A over the rows: the waves lay
-// those operands down in LDS (43 KB) and share the 36 gradient tiles over the
+// those operands down in LDS (21 KB) and share the 36 gradient tiles over the
 // group's rows, and over the groups group, group + grid, ...; the workgroup's
 // sums go to its slice of gpart, where mlp_reduce adds the slices in order
-// (deterministic).  A batch of 4096 is 64 workgroups, bound by the latency of
+// (deterministic).  A batch of 4096 is 128 workgroups, bound by the latency of
 // one group: with a wave per 16 rows, whose lanes have 32 tanh in turn and
-// whose weights are loaded layer by layer, 20 us; so 15.
+// whose weights are loaded layer by layer, 20 us; with four waves, 15 in groups
+// of 64 rows (four waves' tanh on a SIMD) and 12 in groups of 32.  Groups of
+// 16 leave more slices to add than they save: a step and a gradient 36.6, 30.5
+// and 38.6 us in groups of 64, 32 and 16.
 constexpr int OP_DY = 0, OP_DZ2 = 2, OP_DZ1 = 6, OP_A2 = 10, OP_A1 = 14, OP_X = 18, OPS = 21;
-constexpr int TRAIN_WAVES = 16, WAVE_TILES = (WG_TILES + TRAIN_WAVES - 1) / TRAIN_WAVES;
+constexpr int ROW_WAVES = TRAIN_ROWS / 16, TRAIN_WAVES = 4 * ROW_WAVES;
+constexpr int WAVE_TILES = (WG_TILES + TRAIN_WAVES - 1) / TRAIN_WAVES;
 
 __global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, const float *X, const float *T, int B) {
-    __shared__ __attribute__((aligned(16))) uint16_t stage[4][2][STAGE_ELEMS];
-    __shared__ v4s op[OPS][4][64];
-    __shared__ float red[4][160];
+    __shared__ __attribute__((aligned(16))) uint16_t stage[ROW_WAVES][2][STAGE_ELEMS];
+    __shared__ v4s op[OPS][ROW_WAVES][64];
+    __shared__ float red[ROW_WAVES][160];
     int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = wave >> 2, c = wave & 3;   // 16 rows of the group, 16 of their columns
@@ -223,8 +227,8 @@ __global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, c
 #pragma unroll
     for (int j = 0; j < WAVE_TILES; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
     float db1 = 0.f, db2 = 0.f, db3 = 0.f, loss = 0.f;
-    for (int g = blockIdx.x; 64 * g < B; g += gridDim.x) {
-        const int row0 = 64 * g + 16 * w, nrows = min(16, B - row0);   // nrows <= 0: no rows left
+    for (int g = blockIdx.x; TRAIN_ROWS * g < B; g += gridDim.x) {
+        const int row0 = TRAIN_ROWS * g + 16 * w, nrows = min(16, B - row0);   // nrows <= 0: no rows left
         asm volatile("" : "+v"(lane));   // addresses are formed here, not kept from before the loop
         const int r = lane & 15, q = lane >> 4;
         float tgt[4];
@@ -234,7 +238,7 @@ __global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, c
             tgt[i] = row < nrows && col < OUT ? T[(size_t)(row0 + row) * OUT + col] : 0.f;
         }
         Forward o;
-        forward16(X, row0, nrows, net, S0, S1, c, lane, o, &op[OP_X][w][lane]);
+        forward16(X, row0, nrows, net, S0, S1, c, lane, o, &op[OP_X][w][lane], ROW_WAVES * 64);
         if (c < 2) {   // dY, its bias sums and the loss (columns 26..31 are zero)
             float d[4];
 #pragma unroll
@@ -288,7 +292,7 @@ __global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, c
             const int oa = tile < 8 ? OP_DY + tile / 4 : (tile < 24 ? OP_DZ2 + (tile - 8) / 4 : OP_DZ1 + (tile - 24) / 3);
             const int ob = tile < 8 ? OP_A2 + tile % 4 : (tile < 24 ? OP_A1 + tile % 4 : OP_X + (tile - 24) % 3);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc[j] = mfma(op[oa][k][lane], op[ob][k][lane], acc[j]);
+            for (int k = 0; k < ROW_WAVES; ++k) acc[j] = mfma(op[oa][k][lane], op[ob][k][lane], acc[j]);
         }
         __syncthreads();   // the operands are replaced by the next group's
     }
@@ -325,8 +329,12 @@ __global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, c
     __syncthreads();
     const int i = threadIdx.x;
     if (i < 128 + OUT + 1) {
-        float v = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
-        if (i == 128 + OUT) v += ((red[0][i + 1] + red[1][i + 1]) + red[2][i + 1]) + red[3][i + 1];
+        float v = red[0][i];
+#pragma unroll
+        for (int k = 1; k < ROW_WAVES; ++k) v += red[k][i];
+        if (i == 128 + OUT)
+#pragma unroll
+            for (int k = 0; k < ROW_WAVES; ++k) v += red[k][i + 1];
         gp[i < 64 ? P_B1 + i : (i < 128 ? P_B2 + i - 64 : (i < 128 + OUT ? P_B3 + i - 128 : NPAR))] = v;
     }
 }
@@ -854,7 +862,7 @@ hipError_t hydro_mlp_launch_forward(const MlpTrain &t, const float *X, int B, fl
 
 static hipError_t launch_rows(const MlpTrain &t, const float *X, const float *T, int B, float *grad, const Adam &ad,
                               float *loss, hipStream_t s) {
-    const int groups = (B + 63) / 64, slices = groups < WG_SLICES ? groups : WG_SLICES;
+    const int groups = (B + TRAIN_ROWS - 1) / TRAIN_ROWS, slices = groups < WG_SLICES ? groups : WG_SLICES;
     hipLaunchKernelGGL(mlp_train_rows, dim3(slices), dim3(64 * TRAIN_WAVES), 0, s, t, X, T, B);
     hipLaunchKernelGGL(mlp_reduce, dim3((NPAR + 64) / 64), dim3(256), 0, s, t, slices, B, grad, ad, loss);
     return hipGetLastError();

@@ -1,5 +1,5 @@
 """The network's forward pass and gradients at the edges of their tiles: 16
-rows in four waves, 64 a workgroup, 64 workgroups before a workgroup takes a
+rows in four waves, 32 a workgroup, 128 workgroups before a workgroup takes a
 second group of rows.
 
 Tolerances: a row's outputs do not depend on the batch (bit for bit); loss
