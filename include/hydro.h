@@ -265,7 +265,7 @@ int hydro_autotune(hydro_t *h, const hydro_grid *g, const char *cache_path, int3
  * step of hydro_step (plain PPM, the column-walk kernel, one launch per
  * stage), without a handle.  Its workspace -- the stage-1 state, the column
  * walk's flux differences, per-leaf signal speeds when amax is NULL and the
- * status word, 7.3 MB for HYDRO_NOALLOC_MAX_LEAVES leaves -- is one fixed
+ * status word, 7.4 MB for HYDRO_NOALLOC_MAX_LEAVES leaves -- is one fixed
  * device array of the library that every GPU it runs on holds until the
  * process ends; the call allocates nothing.  It runs on the calling thread's
  * current device, in place on g->U (8^3 leaves; g->n <= HYDRO_NOALLOC_MAX_LEAVES,
