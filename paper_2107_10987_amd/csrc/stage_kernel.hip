@@ -1304,11 +1304,11 @@ hipError_t hydro_launch_stage(const StageArgs &a, hipStream_t s) {
 // a leaf, wave f field f and a lane a cell, with the 12 x 12 x 5 box of the
 // layer's stencils in LDS (40 KB: two workgroups per compute unit, and eight
 // times as many as leaves), runs each of the 13 lines once for both its ends,
-// and hands its rows over through 4 KB of LDS of its own, so that they go out
-// as runs of consecutive words (a lane storing its own row touches a line per
-// lane and store) and no wave waits for another.  125 leaves: 109 us with a
-// workgroup per leaf, one point at a time and rows stored by their lanes,
-// 38 us so.
+// and lays the rows of half the layer's cells down in LDS as they lie in memory
+// (30 KB), to go out in 16-byte stores of whole lines (of words where the
+// caller's buffers are not aligned to them).  125 leaves: 109 us with a
+// workgroup per leaf, one point at a time and rows stored by their lanes (a
+// line per lane and store), 35 with each wave's rows as runs of words, 32 so.
 constexpr int PBX = NX + 4;                       // box edge in x and y
 constexpr int PBN = PBX * PBX * 5;                // box cells
 constexpr int XIN = mlp::IN, TOUT = mlp::OUT;
@@ -1326,7 +1326,7 @@ __global__ void __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(4)
                                                         const int32_t *prolong, int n_prolong, float *X,
                                                         float *T, uint8_t *valid) {
     __shared__ double box[NF][PBN];
-    __shared__ float rows[NF][32 * XIN];
+    __shared__ __attribute__((aligned(16))) float rows[32 * NF * XIN];
     const int leaf = blockIdx.x / NX, layer = blockIdx.x % NX, tid = threadIdx.x;
     for (int e = tid; e < PBN; e += 64 * NF) {
         const int i = e % PBX - 2, j = (e / PBX) % PBX - 2, k = e / (PBX * PBX) + layer - 2;
@@ -1355,17 +1355,22 @@ __global__ void __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(4)
     const double rs = sigma > 0.0 ? 1.0 / sigma : 0.0;
     const size_t row0 = ((size_t)leaf * NC + layer * 64) * NF;   // the layer's rows, cell by cell
     valid[row0 + cell * NF + f] = sigma > 0.0 ? 1 : 0;
-    // a half of the wave's rows at a time through the wave's own buffer
-    float *buf = rows[f];
+    // half of the layer's cells at a time through LDS, as they lie in memory
+    const bool wide = (((uintptr_t)X | (uintptr_t)T) & 15) == 0;
     auto hand_over = [&](float *out, int cols, int h) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS is in order within a wave
-        float *o = out + (row0 + (size_t)(32 * h) * NF + f) * cols;
-        for (int e = cell; e < 32 * cols; e += 64) o[(size_t)(e / cols) * NF * cols + e % cols] = buf[e];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __syncthreads();
+        float *o = out + (row0 + (size_t)(32 * h) * NF) * cols;
+        const int n = 32 * NF * cols;
+        if (wide) {
+            for (int e = tid; e < n / 4; e += 64 * NF) ((float4 *)o)[e] = ((const float4 *)rows)[e];
+        } else {
+            for (int e = tid; e < n; e += 64 * NF) o[e] = rows[e];
+        }
+        __syncthreads();
     };
     for (int h = 0; h < 2; ++h) {
         if (cell / 32 == h) {
-            float *x = buf + (cell % 32) * XIN;
+            float *x = rows + ((cell % 32) * NF + f) * XIN;
 #pragma unroll
             for (int o = 0; o < 27; ++o) x[o] = (float)((q[offset(o)] - qc) * rs);
 #pragma unroll
@@ -1385,7 +1390,7 @@ __global__ void __launch_bounds__(64 * NF) __attribute__((amdgpu_waves_per_eu(4)
     for (int h = 0; h < 2; ++h) {
         if (cell / 32 == h) {
 #pragma unroll
-            for (int o = 0; o < TOUT; ++o) buf[(cell % 32) * TOUT + o] = tv[o];
+            for (int o = 0; o < TOUT; ++o) rows[((cell % 32) * NF + f) * TOUT + o] = tv[o];
         }
         hand_over(T, TOUT, h);
     }

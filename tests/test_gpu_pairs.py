@@ -52,3 +52,27 @@ def test_pairs_match_oracle(bc, prolong):
                 assert np.array_equal(X[row], x.astype(np.float32))
                 cell = (k + 1) * 100 + (j + 1) * 10 + (i + 1)
                 assert np.array_equal(T[row], ((V[cell, :, f] - nb[13]) * (1.0 / s)).astype(np.float32))
+
+
+@pytest.mark.parametrize("x_off,t_off", [(1, 0), (0, 1), (2, 3), (4, 4)])
+def test_buffers_of_any_alignment(x_off, t_off):
+    import torch
+    from paper_2107_10987_amd.hydro import Hydro, _ptr, C
+    print("case: pairs, offsets", x_off, t_off, flush=True)
+    t = two_levels(PERIODIC)
+    n = t.n * 512 * 7
+    U = torch.tensor(np.random.default_rng(3).uniform(0.5, 2.0, (t.n, 7, 8, 8, 8)), device="cuda")
+    hy = Hydro(max_leaves=t.n)
+    try:
+        g = hy.grid(t, U, 0.0, GAMMA)
+        X, T, valid = hy.mlp_pairs(g)
+        mx, mt = (torch.full((n * c + 8,), 7.0, device="cuda") for c in (34, 26))
+        v = torch.empty(n, dtype=torch.uint8, device="cuda")
+        hy._check(hy.L.hydro_mlp_pairs(hy.h, C.byref(g.c), _ptr(mx[x_off:]), _ptr(mt[t_off:]), _ptr(v)))
+    finally:
+        hy.close()
+    for m, off, whole in ((mx, x_off, X), (mt, t_off, T)):
+        k = whole.numel()
+        assert torch.equal(m[off:off + k], whole.reshape(-1))
+        assert bool((m[:off] == 7.0).all()) and bool((m[off + k:] == 7.0).all())   # nothing beside the rows
+    assert torch.equal(v, valid)
