@@ -621,20 +621,26 @@ constexpr int NTC = 768;            // 12 waves x 64 lanes: three per SIMD
 static_assert(NTC == 64 * PART_WAVES, "waves of a part");
 constexpr int COLS_PER_WAVE = 6;    // 6 columns x 10 cells = 60 lanes
 
-// PPM on five values along a line, as the column walk computes it: the limited
-// parabola of ppm_vals in differences from the middle value, in 46
+// PPM on five values along a line, as the column walk computes it: ppm_vals
+// with its slopes in differences and its constraint as clamps, in 48
 // instructions without a branch where ppm_vals takes 67 with its constraint's
 // branches (the walk issues VALU instructions nearly all the time, so each is
-// time: with the flux below, two steps of a 34,000-leaf binary went from 56.6
-// to 47.0 ms, of 512 blocks of a transonic flow by RK3 from 1.21 to 0.97 ms).
-// With d1..d4 the four differences and sm, s0, sp the limited slopes,
-//   X = 6 (R - q2) = 3 d3 + s0 - sp,   Y = 6 (q2 - L) = 3 d2 + s0 - sm,
-// and the CW84 constraint reads: both zero where X and Y have opposite signs
-// (an extremum), else each at most twice the other (D M6 > D^2 is Y > 2 X,
-// D M6 < -D^2 is X > 2 Y): X clamped to the interval between 0 and 2 Y, Y to
-// that between 0 and 2 X.  Results agree with ppm_vals to the rounding of the
-// offsets; where X or Y is a NaN, which the clamps pass over, the line is to be
-// taken from ppm_vals (returns whether).
+// time: with the flux below, two steps of a 34,000-leaf binary take 48.5 ms and
+// took 56.6, of 512 blocks of a transonic flow by RK3 1.00 and 1.21 ms).
+// With d1..d4 the four differences and sm, s0, sp the limited slopes, the
+// unlimited ends are R and L, and the CW84 constraint reads: both q2 where they
+// lie on the same side of it (an extremum), else each end at most twice as far
+// from q2 as the other (D M6 > D^2 and D M6 < -D^2): R clamped to the interval
+// between q2 and 3 q2 - 2 L, L to that between q2 and 3 q2 - 2 R.
+// R of a cell and L of the next are one expression of the same operands, so
+// where the constraint leaves them the two sides of a face are equal to the bit
+// and their jump, which the dissipation multiplies by the sound speed, is zero.
+// (Clamped as offsets from q2, in two instructions fewer and 3% of a stage, the
+// ends are an ulp apart for one interface in twelve of a smooth profile, and the
+// mean error of a slow flow's mass flux is fifty times as large.)  Where R or L
+// is a NaN, which the clamps pass over, the line is to be taken from ppm_vals
+// (returns whether); min_of and max_of, so that a q2 from memory is not quieted
+// first: one that needs it gives a NaN.
 __device__ __forceinline__ bool ppm_walk(double q0, double q1, double q2, double q3, double q4, double &left,
                                          double &right) {
     const double d1 = q1 - q0, d2 = q2 - q1, d3 = q3 - q2, d4 = q4 - q3;
@@ -645,16 +651,15 @@ __device__ __forceinline__ bool ppm_walk(double q0, double q1, double q2, double
     const double sm = copysign(mm, d1) + copysign(mm, d2);
     const double s0 = copysign(m0, d2) + copysign(m0, d3);
     const double sp = copysign(mp, d3) + copysign(mp, d4);
-    const double X = __builtin_fma(3.0, d3, s0 - sp), Y = __builtin_fma(3.0, d2, s0 - sm);
-    const double X2 = X + X, Y2 = Y + Y;
-    const double Xc = fmax(fmin(Y2, 0.0), fmin(X, fmax(Y2, 0.0)));
-    const double Yc = fmax(fmin(X2, 0.0), fmin(Y, fmax(X2, 0.0)));
-    right = __builtin_fma(Xc, 1.0 / 6.0, q2);
-    left = __builtin_fma(-Yc, 1.0 / 6.0, q2);
+    const double R = __builtin_fma(s0 - sp, 1.0 / 6.0, __builtin_fma(0.5, d3, q2));
+    const double L = __builtin_fma(sm - s0, 1.0 / 6.0, __builtin_fma(0.5, d2, q1));
+    const double maxR = __builtin_fma(3.0, q2, -(L + L)), maxL = __builtin_fma(3.0, q2, -(R + R));
+    right = mlp::max_of(mlp::min_of(R, q2), mlp::min_of(mlp::max_of(R, q2), maxR));
+    left = mlp::max_of(mlp::min_of(L, q2), mlp::min_of(mlp::max_of(L, q2), maxL));
     // formed here: sunk to their uses behind the flux's branches, the selects
     // would keep four registers alive per value instead of two
     asm volatile("" : "+v"(right), "+v"(left));
-    return __builtin_isunordered(X, Y);
+    return __builtin_isunordered(R, L);
 }
 
 // Both ends of the line through padded cell c along d = (dx,dy,dz) for all
