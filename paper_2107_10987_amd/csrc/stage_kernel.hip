@@ -188,8 +188,11 @@ __device__ __forceinline__ double side_state(const Axis &e, const double U[NF], 
                                              const Phys &ph, double &mn, double &vn, double &un, double &p) {
     const double E = U[EGAS];
     const double rinv = rcp_nr(U[RHO]);
-    const double ss = __builtin_fma(U[SZ], U[SZ], __builtin_fma(U[SY], U[SY], U[SX] * U[SX]));
-    double eint = __builtin_fma(-0.5 * rinv, ss, E);
+    // the dual-energy switch without contraction, as the other kernels decide
+    // it: E less the rounded kinetic energy (whose halving is exact, so that it
+    // goes into the subtraction); fused it takes two instructions fewer, 0.6%
+    const double ss = U[SX] * U[SX] + U[SY] * U[SY] + U[SZ] * U[SZ];
+    double eint = __builtin_fma(-0.5, ss * rinv, E);
     if (eint < ph.eta1 * E) eint = pow_tau(U[TAU], ph.gamma);
     mn = __builtin_fma(e.ez, U[SZ], __builtin_fma(e.ey, U[SY], e.ex * U[SX]));
     vn = mn * rinv;

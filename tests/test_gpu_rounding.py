@@ -1,6 +1,8 @@
 """The rounding of the column walk: the two sides of an interface agree to the
-bit where no limiter acts, and L(U) is no further from its 80-bit value than a
-plain FP64 evaluation."""
+bit where no limiter acts, L(U) is no further from its 80-bit value than a
+plain FP64 evaluation, and the dual-energy switch decides as it is written."""
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -95,3 +97,44 @@ def test_rounding_error_of_the_rhs(kind, nb, limit):
     err = [np.array([np.abs((a - exact) / dt)[:, f][inner].mean() for f in range(7)], np.float64) for a in (got, plain)]
     print("mean error against the oracle's:", np.array2string(err[0] / err[1], precision=2), flush=True)
     assert np.all(err[0] <= limit * err[1]), err
+
+
+def switch_states():
+    """Uniform states whose internal energy falls on the other side of
+    eta1 E when the kinetic energy is formed with fused multiply-adds: four
+    that take tau's pressure as the switch is written, four that do not."""
+    def fma(a, b, c):
+        return float(Fraction(a) * Fraction(b) + Fraction(c))
+    r = np.random.default_rng(4)
+    out = {True: [], False: []}
+    while min(map(len, out.values())) < 4:
+        rho = 2.0 ** int(r.integers(-1, 2))   # 1 / rho exact on both sides
+        s = r.uniform(0.5, 2.0, 3)
+        rinv = 1.0 / rho
+        ek = 0.5 * (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) * rinv
+        E = ek / (1.0 - 1e-3) * (1.0 + 2.0 ** -52 * int(r.integers(-4, 5)))
+        fused = fma(-0.5 * rinv, fma(s[2], s[2], fma(s[1], s[1], s[0] * s[0])), E) < 1e-3 * E
+        written = E - ek < 1e-3 * E
+        if fused != written and len(out[bool(written)]) < 4:
+            out[bool(written)].append((rho, *s, E, 1.0, 0.5))
+    return out[True] + out[False]
+
+
+@pytest.mark.parametrize("schedule", ["face", "column", "tiled"])
+def test_dual_energy_switch_as_written(schedule):
+    """At the threshold the pressure jumps (tau = 1 here, e = 1e-3 E): signal
+    speeds as the oracle's, to the sound speed's rounding."""
+    import torch
+    import oracle
+    from paper_2107_10987_amd.hydro import Hydro
+    t = uniform_tree((1, 1, 1), (PERIODIC,) * 3, (0.0, 0.0, 0.0), 1.0 / 8)
+    o = oracle.Oracle(t, GAMMA, 0.0)
+    hy = Hydro(max_leaves=1, schedule=schedule)
+    try:
+        for k, q in enumerate(switch_states()):
+            print("case: state", k, schedule, flush=True)
+            U = np.ascontiguousarray(np.broadcast_to(np.array(q)[None, :, None, None, None], (1, 7, 8, 8, 8)))
+            a = hy.signal_speed(hy.grid(t, torch.tensor(U, device="cuda"), 0.0, GAMMA)).cpu().numpy()
+            assert abs(a[0] - o.signal_speed(U)[0]) <= 1e-12 * a[0], (k, a, o.signal_speed(U))
+    finally:
+        hy.close()
