@@ -245,7 +245,9 @@ int hydro_graph_launch(hydro_t *h, void *stream);
 
 /* Time every schedule on stage-1 launches of 1, 2, 4, ... leaves (up to
  * g->n, each bucket from the first leaves of g) and keep the fastest per
- * size bucket for HYDRO_SCHED_AUTO; table (host [HYDRO_NBUCKET], may be
+ * size bucket for HYDRO_SCHED_AUTO (in a table HYDRO_SCHED_TILED stands for
+ * parts of leaves only: it is timed where they all run at once, and sizes of
+ * its bucket past that take HYDRO_SCHED_COLUMN); table (host [HYDRO_NBUCKET], may be
  * NULL) receives it, and cache_path (may be NULL) a JSON copy.  When g has
  * several launches per stage (which run concurrently), whole stages of that
  * partition are also timed with the table and with each schedule for every

@@ -200,13 +200,6 @@ int set_device(hydro_t *h) {
     return e == hipSuccess ? HYDRO_OK : hip_fail(h, e, "hipSetDevice");
 }
 
-// Launch one stage over all leaves, split as the grid asks.
-int bucket_of(int nleaf) {
-    int b = 0;
-    while ((2 << b) <= nleaf && b < HYDRO_NBUCKET - 1) ++b;
-    return b;
-}
-
 // The autotuner's choice for a grid's launch partition that replaces it by
 // one launch over all its leaves (the ranges are consecutive, from 0 to n),
 // with the per-size table's schedule.
@@ -216,36 +209,12 @@ constexpr int MULTI_MERGE = 5;
 int resolve_schedule(const hydro_t *h, int nleaf, int nstage, bool concurrent) {
     if (h->p.schedule != HYDRO_SCHED_AUTO) return h->p.schedule;
     if (concurrent && h->multi_sched >= 0 && h->multi_sched != MULTI_MERGE) return h->multi_sched;
-    if (h->table_loaded) return h->table[bucket_of(nleaf)];
+    if (h->table_loaded) return table_schedule(h->table, nleaf, h->num_cu);
     // built-in rule: parts of leaves where whole ones leave half the chip idle
     return (2 * nstage <= h->num_cu) ? HYDRO_SCHED_TILED : HYDRO_SCHED_COLUMN;
 }
 
-// alone: no other launch of the stage runs beside this one.
-void set_schedule(const hydro_t *h, StageArgs &a, int sched, bool alone) {
-    a.kernel = KERNEL_COLUMN;
-    a.tiles = 1;
-    a.whole = a.nleaf;
-    switch (sched) {
-    case HYDRO_SCHED_FACE: a.kernel = KERNEL_FACE; break;
-    case HYDRO_SCHED_PERSISTENT: a.kernel = KERNEL_PERSISTENT; break;
-    case HYDRO_SCHED_TILED:
-        a.tiles = leaf_parts(a.nleaf, h->num_cu);
-        a.whole = 0;
-        if (a.tiles == 1) {   // a queue of axis tiles
-            a.kernel = KERNEL_PERSISTENT;
-            a.tiles = 3;
-        }
-        break;
-    default:
-        // a last round that would leave half the chip idle runs as parts
-        if (alone && a.nleaf > h->num_cu && a.nleaf % h->num_cu) {
-            a.tiles = leaf_parts(a.nleaf % h->num_cu, h->num_cu);
-            if (a.tiles > 1) a.whole = a.nleaf - a.nleaf % h->num_cu;
-        }
-    }
-}
-
+// Launch one stage over all leaves, split as the grid asks.
 int run_stage(hydro_t *h, const hydro_grid *g, int stage, double dt, const double *Uin,
               const double *Un, double *Uout, double *amax, int accumulate,
               const double *dt_dev = nullptr, bool allow_timing = true) {
@@ -318,7 +287,10 @@ int run_stage(hydro_t *h, const hydro_grid *g, int stage, double dt, const doubl
         const int j = k++ % nst;
         const hipStream_t st = j == 0 ? s : h->side[j - 1];
         a.queue = h->queue + QUEUE_INTS * j;
-        set_schedule(h, a, resolve_schedule(h, a.nleaf, g->n << h->ts, nst > 1), nst == 1);
+        const Split split = split_launch(resolve_schedule(h, a.nleaf, g->n << h->ts, nst > 1), a.nleaf, nst == 1, h->num_cu);
+        a.kernel = split.kernel;
+        a.tiles = split.tiles;
+        a.whole = split.whole;
         if (h->p.recon == 1) {
             // the network's point values and per-cell verdicts for this launch
             mlp::MlpInfer m{};
@@ -890,6 +862,7 @@ int hydro_autotune(hydro_t *h, const hydro_grid *g, const char *cache_path, int3
         int best = HYDRO_SCHED_COLUMN;
         for (int sc = HYDRO_SCHED_FACE; sc <= HYDRO_SCHED_TILED && rc == HYDRO_OK; ++sc) {
             if (sc == HYDRO_SCHED_FACE && h->p.recon == 1) continue;   // no learned variant (runs the column walk)
+            if (sc == HYDRO_SCHED_TILED && leaf_parts(size << h->ts, h->num_cu) == 1) continue;   // not what a table's TILED runs
             h->p.schedule = sc;
             const int reps = size >= 256 ? 3 : 10;
             rc = run_stage(h, &sub, 1, 0.0, g->U, g->U, h->U1, h->amax, 0, nullptr, false);   // warm

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "schedule.h"
+
 namespace hydro {
 
 constexpr int NX = 8;                      // cells per leaf edge
@@ -55,7 +57,7 @@ struct StageArgs {
     double ca, cb;            // stage > 1: Uout = ca Un + cb (Uin + dt L)
     int centre_only;          // old scheme: one flux point per face, weight 1
     int amax_accumulate;      // stage 2 of a step: amax = max(amax, this stage)
-    int kernel;               // KERNEL_* below
+    int kernel;               // KERNEL_* of schedule.h
     double *dscr;             // column walk: [n][3][7][512] per-axis flux differences
     const double *dt_dev;     // if set, dt is read from device memory
     // column walk over parts of leaves
@@ -203,23 +205,11 @@ struct RefluxArgs {
     int ts, lg;               // blocks per leaf (log2), leaf edge (log2)
 };
 
-enum Kernel { KERNEL_FACE = 0, KERNEL_COLUMN = 1, KERNEL_PERSISTENT = 2 };
-
 // XCDs of the chip (workgroups are dispatched round-robin over them) and the
 // persistent queue's counters: one per XCD's item range, then the count of
 // finished workgroups.
 constexpr int NXCD = 8;
 constexpr int QUEUE_INTS = 16;
-
-// Workgroups per leaf of `left` blocks that have num_cu compute units to
-// themselves, so that all of them run at once; 1 where whole leaves take more
-// than half of them (150 leaves as 300 halves: two rounds of 45 us against one
-// of 71).
-inline int leaf_parts(int left, int num_cu) {
-    for (int t : {8, 4, 3, 2})
-        if ((int64_t)t * left <= num_cu) return t;
-    return 1;
-}
 
 // Leaf (within a launch of n leaves, one workgroup each) of workgroup b.
 // Workgroups are dispatched round-robin over the chip's 8 XCDs (b runs on
