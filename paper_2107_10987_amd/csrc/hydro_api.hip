@@ -205,13 +205,11 @@ int set_device(hydro_t *h) {
 // with the per-size table's schedule.
 constexpr int MULTI_MERGE = 5;
 
-// Schedule of a launch of nleaf of the stage's nstage blocks.
-int resolve_schedule(const hydro_t *h, int nleaf, int nstage, bool concurrent) {
+// Schedule of a launch of nleaf blocks beside which `beside` run at one time.
+int resolve_schedule(const hydro_t *h, int nleaf, int beside, bool concurrent) {
     if (h->p.schedule != HYDRO_SCHED_AUTO) return h->p.schedule;
     if (concurrent && h->multi_sched >= 0 && h->multi_sched != MULTI_MERGE) return h->multi_sched;
-    if (h->table_loaded) return table_schedule(h->table, nleaf, h->num_cu);
-    // built-in rule: parts of leaves where whole ones leave half the chip idle
-    return (2 * nstage <= h->num_cu) ? HYDRO_SCHED_TILED : HYDRO_SCHED_COLUMN;
+    return h->table_loaded ? table_schedule(h->table, nleaf, beside, h->num_cu) : auto_schedule(beside, h->num_cu);
 }
 
 // Launch one stage over all leaves, split as the grid asks.
@@ -287,7 +285,8 @@ int run_stage(hydro_t *h, const hydro_grid *g, int stage, double dt, const doubl
         const int j = k++ % nst;
         const hipStream_t st = j == 0 ? s : h->side[j - 1];
         a.queue = h->queue + QUEUE_INTS * j;
-        const Split split = split_launch(resolve_schedule(h, a.nleaf, g->n << h->ts, nst > 1), a.nleaf, nst == 1, h->num_cu);
+        const int beside = blocks_beside(a.nleaf, g->n << h->ts, nonempty, nst);
+        const Split split = split_launch(resolve_schedule(h, a.nleaf, beside, nst > 1), a.nleaf, beside, nst == 1, h->num_cu);
         a.kernel = split.kernel;
         a.tiles = split.tiles;
         a.whole = split.whole;

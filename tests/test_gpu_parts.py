@@ -83,3 +83,21 @@ def test_parts_in_a_graph():
     finally:
         eager.close()
         graph.close()
+
+
+@pytest.mark.parametrize("n,per", [(96, 48), (128, 32), (60, 3), (300, 38)])
+def test_parts_in_launches_side_by_side(n, per):
+    """Launches that share the chip are split by what runs beside them."""
+    import torch
+    from paper_2107_10987_amd.hydro import Hydro
+    print("case: parts in launches,", n, "in", per, flush=True)
+    t = uniform_tree((n, 1, 1), (PERIODIC,) * 3, (0.0, 0.0, 0.0), 1.0 / 16)
+    U = rough(n)
+    whole = two_steps(t, U, "persistent")
+    hy = Hydro(max_leaves=n)
+    try:
+        g = hy.grid(t, torch.tensor(U, device="cuda"), OMEGA, GAMMA, launch_off=list(range(0, n, per)) + [n])
+        a = np.stack([hy.step(g, 2e-3) for _ in range(2)])
+        assert np.array_equal(whole[0], g.U.cpu().numpy()) and np.array_equal(whole[1], a)
+    finally:
+        hy.close()

@@ -14,9 +14,11 @@ using namespace hydro;
 extern "C" {
 int bucket(int n) { return bucket_of(n); }
 int parts(int n, int cu) { return leaf_parts(n, cu); }
-int table(const int32_t *t, int n, int cu) { return table_schedule(t, n, cu); }
-void split(int sched, int n, int alone, int cu, int *o) {
-    const Split s = split_launch(sched, n, alone, cu);
+int beside(int n, int nstage, int nlaunch, int streams) { return blocks_beside(n, nstage, nlaunch, streams); }
+int automatic(int beside, int cu) { return auto_schedule(beside, cu); }
+int table(const int32_t *t, int n, int beside, int cu) { return table_schedule(t, n, beside, cu); }
+void split(int sched, int n, int beside, int alone, int cu, int *o) {
+    const Split s = split_launch(sched, n, beside, alone, cu);
     o[0] = s.kernel, o[1] = s.tiles, o[2] = s.whole;
 }
 }
@@ -44,7 +46,7 @@ def test_every_size_splits_into_whole_and_parts(rules, cu):
     for n in range(1, 4 * cu):
         for sched in (FACE, COLUMN, PERSISTENT, TILED):
             for alone in (0, 1):
-                kernel, tiles, whole = split(rules, sched, n, alone, cu)
+                kernel, tiles, whole = split(rules, sched, n, n, alone, cu)
                 if kernel == 1:   # direct: a workgroup a whole block, parts for the rest, which run at once
                     assert 0 <= whole <= n and tiles in (1, 2, 3, 4, 8)
                     assert (whole == n) == (tiles == 1)
@@ -61,9 +63,29 @@ def test_table_takes_tiled_as_parts_only(rules, cu):
     queue of axis items."""
     table = (C.c_int32 * 16)(*[TILED] * 16)
     for n in range(1, 4 * cu):
-        s = rules.table(table, n, cu)
+        s = rules.table(table, n, n, cu)
         assert s == (TILED if 2 * n <= cu else COLUMN), n
-        assert split(rules, s, n, 1, cu)[0] == 1
+        assert split(rules, s, n, n, 1, cu)[0] == 1
     for other in (FACE, COLUMN, PERSISTENT):
         table = (C.c_int32 * 16)(*[other] * 16)
-        assert {rules.table(table, n, cu) for n in range(1, 4 * cu)} == {other}
+        assert {rules.table(table, n, n, cu) for n in range(1, 4 * cu)} == {other}
+
+
+@pytest.mark.parametrize("cu", [32, 256, 304])
+def test_launches_side_by_side_share_the_chip(rules, cu):
+    """Equal launches on up to four streams: their parts fit at once as far as
+    blocks_beside says how many run, and small launches go in parts however
+    many of them a stage has."""
+    for n in range(1, cu):
+        for nlaunch in (1, 2, 3, 4, 5, 16, 60):
+            streams = min(4, nlaunch)
+            beside = rules.beside(n, n * nlaunch, nlaunch, streams)
+            assert max(n, 4 * n * streams // 5) <= beside <= n * streams
+            sched = rules.automatic(beside, cu)
+            assert (sched == TILED) == (2 * beside <= cu)
+            kernel, tiles, whole = split(rules, sched, n, beside, int(streams == 1), cu)
+            assert kernel == 1 and (whole, tiles) == (n, 1) if sched == COLUMN else tiles * beside <= cu
+            kernel, tiles, whole = split(rules, TILED, n, beside, int(streams == 1), cu)
+            assert kernel == (1 if 2 * n <= cu else 2) and tiles >= 2
+    assert rules.beside(10, 600, 60, 4) == 32 and rules.automatic(32, 256) == TILED   # was whole leaves
+    assert split(rules, TILED, 32, rules.beside(32, 128, 4, 4), 0, 256)[1] == 2       # was eight parts
