@@ -6,7 +6,7 @@ runs twice, so that its counters are seen to be left at zero."""
 import numpy as np
 import pytest
 
-from paper_2107_10987_amd.workloads import PERIODIC, uniform_tree
+from paper_2107_10987_amd.workloads import PERIODIC, LeafSet, uniform_tree
 
 pytestmark = pytest.mark.gpu
 
@@ -101,3 +101,57 @@ def test_parts_in_launches_side_by_side(n, per):
         assert np.array_equal(whole[0], g.U.cpu().numpy()) and np.array_equal(whole[1], a)
     finally:
         hy.close()
+
+
+def refined(nb, corners):
+    ls = LeafSet((nb,) * 3, (PERIODIC,) * 3, (0.0, 0.0, 0.0), 1.0 / (8 * nb),
+                 [(0, i, j, k) for i in range(nb) for j in range(nb) for k in range(nb)])
+    for c in corners:
+        ls.refine(0, c)
+    return ls.tree()
+
+
+def wavy(tree):
+    x, y, z = np.moveaxis(2 * np.pi * tree.cell_centres(), 1, 0)
+    # (a jump of 12 in density: the learned path's cells there fall back)
+    rho = (1.0 + 0.4 * np.sin(x + 0.3) * np.cos(2 * y)) * np.where(x + y < 4.0, 12.0, 1.0)
+    v = [0.4 * np.sin(y + z), 0.3 * np.cos(x + 0.1) * np.sin(z), 0.3 * np.sin(2 * x + y)]
+    e = 1.5 + 0.4 * np.cos(z + x)
+    return np.ascontiguousarray(np.stack([rho, rho * v[0], rho * v[1], rho * v[2],
+                                          e + 0.5 * rho * sum(q * q for q in v), e ** (1 / GAMMA),
+                                          rho * (0.5 + 0.3 * np.sin(x + y + z))], axis=1))
+
+
+# 22 leaves in 8 parts, 120 in 2, 258 as a whole round and two leaves in 8
+REFINED = [(2, [(0, 0, 0), (1, 1, 1)]), (4, [(i, j, k) for i in (0, 2) for j in (0, 2) for k in (0, 2)]),
+           (6, [(0, 0, 0), (2, 2, 0), (4, 4, 0), (0, 2, 3), (2, 4, 3), (4, 0, 3)])]
+
+
+@pytest.mark.parametrize("opts", [dict(reflux=True), dict(prolong=True), dict(learned=True),
+                                  dict(reflux=True, prolong=True, learned=True)],
+                         ids=lambda o: "+".join(o))
+@pytest.mark.parametrize("nb,corners", REFINED, ids=["22", "120", "258"])
+def test_parts_on_refined_meshes(nb, corners, opts):
+    """Coarse/fine faces corrected, prolonged ghosts and learned values."""
+    import torch
+    from paper_2107_10987_amd.hydro import Hydro
+    t = refined(nb, corners)
+    print("case: parts,", t.n, "leaves", opts, flush=True)
+    U = torch.tensor(wavy(t), device="cuda")
+    out = []
+    for schedule in ("persistent", "auto"):
+        hy = Hydro(max_leaves=t.n, schedule=schedule, **opts)
+        try:
+            if hy.learned:
+                hy.mlp_load(np.random.default_rng(3).normal(0.0, 0.15, 8090))
+            g = hy.grid(t, U.clone(), OMEGA, GAMMA)
+            assert not hy.reflux or g.n_reflux > 0
+            assert not hy.prolong or g.ptable is not None
+            a = [hy.step(g, 1e-3) for _ in range(2)]
+            if hy.learned:
+                cells, fallback = hy.mlp_stats()
+                assert 0 < fallback < cells
+            out.append((g.U.cpu().numpy(), np.stack(a)))
+        finally:
+            hy.close()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])

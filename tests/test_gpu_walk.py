@@ -116,3 +116,57 @@ def test_nan_spreads_as_in_the_oracle():
             hy.check()
     finally:
         hy.close()
+
+
+@pytest.mark.parametrize("kind", ["rough", "ties", "plateaus"])
+def test_face_centre_scheme_against_oracle(kind):
+    """One point per face with weight one: the face-normal line alone."""
+    import torch
+    import oracle
+    from paper_2107_10987_amd.hydro import Hydro
+    t = uniform_tree((3, 2, 2), (PERIODIC,) * 3, (-0.2, 0.1, 0.0), 1.0 / 16)
+    U = state(kind, t.n, 13)
+    print("case: face centres,", kind, flush=True)
+    o = oracle.Oracle(t, GAMMA, 0.3, centre_only=True)
+    hy = Hydro(max_leaves=t.n, schedule="column", centre_only=True)
+    try:
+        g = hy.grid(t, torch.tensor(U, device="cuda"), 0.3, GAMMA)
+        dt = 0.2 * o.dt(U)
+        want, a = o.stage(1, dt, U)
+        out = torch.empty_like(g.U)
+        am = torch.zeros(t.n, dtype=torch.float64, device="cuda")
+        hy.stage(g, 1, dt, g.U, None, out, am)
+        assert np.abs(am.cpu().numpy() - a).max() <= 1e-12 * a.max()
+        check(out.cpu().numpy(), want, o, U, label=kind)
+    finally:
+        hy.close()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** 100, 2.0 ** -100])
+def test_huge_and_tiny_values_against_oracle(scale):
+    """The scheme is homogeneous in the conserved fields (the entropy tracer by
+    its own exponent), so a state times 2^100 or 2^-100, its tracer to match,
+    gives that times the result and the same speeds: checked against the
+    oracle at unit scale."""
+    import torch
+    import oracle
+    from paper_2107_10987_amd.hydro import Hydro
+    t = uniform_tree((2, 2, 1), (PERIODIC,) * 3, (0.0, 0.0, 0.0), 1.0 / 16)
+    U = state("rough", t.n, 19)
+    print("case: scale", scale, flush=True)
+    factor = np.full(7, scale)
+    factor[5] = scale ** (1 / GAMMA)
+    o = oracle.Oracle(t, GAMMA, 0.3)
+    dt = 0.2 * o.dt(U)
+    want, a = o.stage(1, dt, U)
+    f = factor[None, :, None, None, None]
+    hy = Hydro(max_leaves=t.n, schedule="column")
+    try:
+        g = hy.grid(t, torch.tensor(U * f, device="cuda"), 0.3, GAMMA)
+        out = torch.empty_like(g.U)
+        am = torch.zeros(t.n, dtype=torch.float64, device="cuda")
+        hy.stage(g, 1, dt, g.U, None, out, am)
+        assert np.abs(am.cpu().numpy() - a).max() <= 1e-12 * a.max()
+        check(out.cpu().numpy() / f, want, o, U, label="scale")
+    finally:
+        hy.close()
