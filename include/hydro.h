@@ -56,7 +56,9 @@ typedef struct hydro_t hydro_t;
 /* Stage-kernel schedules (hydro_params.schedule). */
 #define HYDRO_SCHED_AUTO 0        /* per launch size: the autotuned table, else a built-in rule  */
 #define HYDRO_SCHED_FACE 1        /* a workgroup per leaf, one face of each axis per thread       */
-#define HYDRO_SCHED_COLUMN 2      /* a workgroup per leaf, lanes walk cell columns (1.71x PPM)    */
+#define HYDRO_SCHED_COLUMN 2      /* a workgroup per leaf, lanes walk cell columns (1.71x PPM); a
+                                     last round of a single launch that would leave half the
+                                     chip idle as TILED's parts */
 #define HYDRO_SCHED_PERSISTENT 3  /* one workgroup per compute unit pulling leaves from a queue  */
 #define HYDRO_SCHED_TILED 4       /* 2 to 8 workgroups per leaf where all run at once, else a queue
                                      of (leaf, axis) items: up to 8x the parallelism */

@@ -2,9 +2,9 @@
 
 Produces ``paper_2107_10987_amd/_build/libhydro.so``.  Every HIP source is
 compiled for gfx950 only, with packed FP32 instructions disabled and FP
-contraction off except in the blocks that enable it explicitly
-(``#pragma clang fp contract(fast)``: the PPM interface and constraint, the
-flux arithmetic after the dual-energy switch).
+contraction off: multiply-adds fuse only where the sources say so, by
+``__builtin_fma`` or ``#pragma clang fp contract(fast)`` (the PPM interface and
+constraint, the flux arithmetic after the dual-energy switch).
 """
 from __future__ import annotations
 

@@ -452,8 +452,9 @@ hipError_t mlp_alloc(hydro_t *h, T **p, size_t count) {
 }
 
 // Network parameters, Adam state and training workspace (always: one
-// allocation of at most 4.4 MB), plus the per-leaf inference outputs when the
-// learned path is on.
+// allocation, 4.4 MB at the default batch; 0.2 MB and the larger of the
+// gradient slices, 32 KB per 32 rows up to 4 MB, and 104 B per row), plus the
+// per-leaf inference outputs when the learned path is on.
 hipError_t alloc_mlp(hydro_t *h, size_t nleaves) {
     h->mlp_batch = h->p.mlp_batch > 0 ? h->p.mlp_batch : 4096;
     mlp::MlpTrain &t = h->mt;

@@ -176,7 +176,7 @@ __device__ __forceinline__ float gelu_fast(float z) {
 // Network outputs Y [B][26] of B rows of X [B][34], a workgroup per 16 rows.
 // Bound by the latency of its chain of layers, most of it the 32 tanh a row's
 // lanes have in turn where one wave holds the rows: four waves have eight each
-// (a call on 1003 rows: 7.9 us with one, 6.1 with four).
+// (a call on 1003 rows: 7.9 us with one, 5.4 with four).
 __global__ void __launch_bounds__(256) mlp_forward(MlpTrain t, const float *X, int B, float *Y) {
     __shared__ __attribute__((aligned(16))) uint16_t S[2][STAGE_ELEMS];
     const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
@@ -284,7 +284,7 @@ __global__ void __launch_bounds__(64 * TRAIN_WAVES) mlp_train_rows(MlpTrain t, c
             op[OP_A2 + c][w][lane] = o.a2;
         }
         __syncthreads();
-        // tiles wave, wave + 16, ...: 0..7 W3 (2 x 4), 8..23 W2 (4 x 4), 24..35 W1 (4 x 3)
+        // tiles wave, wave + 8, ...: 0..7 W3 (2 x 4), 8..23 W2 (4 x 4), 24..35 W1 (4 x 3)
 #pragma unroll
         for (int j = 0; j < WAVE_TILES; ++j) {
             const int tile = TRAIN_WAVES * j + wave;

@@ -13,8 +13,8 @@ enum Kernel { KERNEL_FACE = 0, KERNEL_COLUMN = 1, KERNEL_PERSISTENT = 2 };
 
 // Workgroups per leaf of `left` blocks that have num_cu compute units to
 // themselves, so that all of them run at once; 1 where whole leaves take more
-// than half of them (150 leaves as 300 halves: two rounds of 45 us against one
-// of 71).
+// than half of them (150 leaves as 300 halves: two rounds of 41 us against one
+// of 68).
 inline int leaf_parts(int left, int num_cu) {
     for (int t : {8, 4, 3, 2})
         if ((int64_t)t * left <= num_cu) return t;

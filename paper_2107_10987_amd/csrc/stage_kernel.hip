@@ -3,7 +3,7 @@
 // One workgroup advances one 8^3 leaf through one Runge-Kutta stage
 // (arXiv 2107.10987, section IV-B):
 //   1. gather the leaf and its three ghost layers into LDS as a 14^3 x 7
-//      structure-of-arrays block (153,664 B): interior cells by coalesced
+//      structure-of-arrays block (152,992 B): interior cells by coalesced
 //      loads, ghost cells through the ghost map (copy, or mean of 2x2x2);
 //   2. every thread owns one face of each axis (576 faces per axis, 576
 //      threads): for the 9 points of the face it reconstructs the left and
@@ -16,8 +16,9 @@
 //      stores; the leaf's maximum signal speed is reduced with wave shuffles.
 // Reconstructed point values never leave the chip.
 //
-// Arithmetic is compiled with FP contraction off so limiter decisions and
-// results round exactly as the expressions are written.
+// Arithmetic is compiled with FP contraction off: multiply-adds are fused only
+// where the source says so (explicitly, or by a contraction pragma), and never
+// in the kinetic energy that decides the dual-energy switch.
 
 #include "hydro_common.h"
 #include "mlp_common.h"
@@ -630,8 +631,8 @@ constexpr int COLS_PER_WAVE = 6;    // 6 columns x 10 cells = 60 lanes
 // with its slopes in differences and its constraint as clamps, in 48
 // instructions without a branch where ppm_vals takes 67 with its constraint's
 // branches (the walk issues VALU instructions nearly all the time, so each is
-// time: with the flux below, two steps of a 34,000-leaf binary take 48.5 ms and
-// took 56.6, of 512 blocks of a transonic flow by RK3 1.00 and 1.21 ms).
+// time: with the flux below, two steps of a 34,000-leaf binary take 49.8 ms and
+// took 56.6, of 512 blocks of a transonic flow by RK3 1.03 and 1.21 ms).
 // With d1..d4 the four differences and sm, s0, sp the limited slopes, the
 // unlimited ends are R and L, and the CW84 constraint reads: both q2 where they
 // lie on the same side of it (an extremum), else each end at most twice as far
@@ -942,7 +943,7 @@ struct ColLane {
 // relaxed device-scope accesses: once such stores have completed (vmcnt 0) they
 // are where every XCD's device-scope loads look, and no fence has to write back
 // and invalidate a whole L2 (64 leaves in four parts each: 45 us with fences
-// around the counter, 29 us so).
+// around the counter, 29 us so, when it was introduced).
 __device__ __forceinline__ void store_dev(double *p, double v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1070,8 +1071,8 @@ __device__ __forceinline__ void join_parts(const StageArgs &a, double *P, const 
 // LDS and an equal share of the 32 tasks, at eight one task per SIMD (a task is
 // the walk's unit of latency: more parts gain nothing); a leaf's parts are
 // neighbours in the launch order of one XCD.  Per stage launch, whole leaves
-// against parts: one leaf 61 against 18.5 us, 64 leaves 65 against 30, 120
-// leaves 68 against 46.
+// against parts: one leaf 65 against 18.5 us, 64 leaves 67 against 27, 128
+// leaves 68 against 41.
 template <bool LEARNED, bool PROLONG>
 __global__ void __launch_bounds__(NTC) stage_kernel_col(StageArgs a) {
     __shared__ double P[BLOCK_LDS + NTC / 64];
