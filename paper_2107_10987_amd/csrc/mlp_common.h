@@ -69,7 +69,9 @@ __device__ __forceinline__ float rz32(double x) {
 }
 
 // fmin and fmax of operands that hold no signalling NaN, which fmin and fmax
-// would first quiet, an instruction each.
+// would first quiet, an instruction each.  (A DPP lane shift may read a result
+// two wait states later at the earliest; behind asm the compiler does not see
+// to that.)
 __device__ __forceinline__ double min_of(double a, double b) {
     double r;
     asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));

@@ -710,6 +710,10 @@ __device__ __forceinline__ void line_ends(const double *P, int c, int dx, int dy
         a3 = b3;
         a4 = b4;
     }
+    // the last end is written by an asm statement, which the compiler does not
+    // know for a vector instruction: the two wait states that a lane shift of it
+    // needs are kept here
+    asm volatile("s_nop 1" : "+v"(pos[NF - 1]));
     if (__builtin_expect(bad, 0)) {   // a NaN among the stencil's values
         const double *qc = P + c;
 #pragma unroll
