@@ -1,6 +1,7 @@
 """The rounding of the column walk: the two sides of an interface agree to the
 bit where no limiter acts, L(U) is no further from its 80-bit value than a
-plain FP64 evaluation, and the dual-energy switch decides as it is written."""
+plain FP64 evaluation, the dual-energy switch decides as it is written, and the
+ends of a steep line are the face kernel's."""
 from fractions import Fraction
 
 import numpy as np
@@ -138,3 +139,26 @@ def test_dual_energy_switch_as_written(schedule):
             assert abs(a[0] - o.signal_speed(U)[0]) <= 1e-12 * a[0], (k, a, o.signal_speed(U))
     finally:
         hy.close()
+
+
+def test_steep_ends_as_the_face_kernel_forms_them():
+    """Energy rising by random factors along x, at rest, density one: a leaf's
+    signal speed is the root of the largest end on its upper face, from lines
+    that both kernels walk the same way, so it is the same to the bit."""
+    import torch
+    from paper_2107_10987_amd.hydro import Hydro
+    print("case: steep ends", flush=True)
+    n = 4096
+    t = uniform_tree((n, 1, 1), (PERIODIC,) * 3, (0.0, 0.0, 0.0), 1.0 / 16)
+    rise = np.random.default_rng(21).uniform(0.0, 3.0, (8 * n // 32, 32)).cumsum(axis=1) - 20.0   # four leaves each
+    cell = np.rint(t.cell_centres()[:, 0] * 16 - 0.5).astype(int)
+    e = np.exp(rise.reshape(-1)[cell])
+    U = conserved(np.ones_like(e), [0.0 * e] * 3, e, 0.5 * np.ones_like(e))
+    speed = []
+    for schedule in ("face", "column"):
+        hy = Hydro(max_leaves=n, schedule=schedule, centre_only=True)
+        try:
+            speed.append(hy.signal_speed(hy.grid(t, torch.tensor(U, device="cuda"), 0.0, GAMMA)).cpu().numpy())
+        finally:
+            hy.close()
+    assert np.array_equal(speed[0], speed[1]), np.count_nonzero(speed[0] != speed[1])
