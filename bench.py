@@ -793,9 +793,10 @@ def profile_mode(torch, args):
         w = sedov_uniform(8)
     if args.copy_probe_mib > 0:
         copy_probe(torch, args.copy_probe_mib)
-    # the learned stage runs with both schedules its autotuner chooses from
-    # for a whole-mesh launch, so that either one's dispatches are counted
-    schedules = ("column", "persistent") if params is not None else ("column",)
+    # the learned stage and the binary's plain one run with both schedules the
+    # autotuner chooses from for a whole-mesh launch, so that either one's
+    # dispatches are counted
+    schedules = ("column", "persistent") if params is not None or name == "binary-plain" else ("column",)
     for sched in schedules:
         hy = Hydro(max_leaves=w.n, schedule=sched, learned=params is not None,
                    centre_only=name == "sedov64-old", leaf_edge=w.tree.leaf_edge)
